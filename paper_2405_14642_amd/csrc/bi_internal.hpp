@@ -131,6 +131,15 @@ struct UniformInst {
     }
 };
 
+// Uniform batch whose results have the operands' n words (mod 2^N).
+struct LowInst {
+    UniformInst u;
+    __device__ __forceinline__ uint64_t count() const { return u.batch; }
+    __device__ __forceinline__ InstRef get(uint64_t p) const {
+        return InstRef{u.a + p * u.n, u.b + p * u.n, u.c + p * u.n, u.n};
+    }
+};
+
 // Block q < k of ONE long operand pair cut into blocks of bw words: words
 // [q bw, min((q + 1) bw, n32)) of a and b (the last block may be shorter).
 struct BlockInst {
@@ -260,6 +269,13 @@ hipError_t launch_bigmul_mfma_big_list(const ListInst &src, uint32_t nmax, uint6
                                        size_t scr_bytes, hipStream_t st, int num_cus);
 hipError_t launch_bigmul_mfma(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n32, uint64_t batch,
                               hipStream_t st, int num_cus);
+
+// The same products of up to conv_small_max(low) words on 16 x 16 x 64 tiles
+// (bi_conv.hpp), one wavefront per row of products.
+uint32_t conv_small_max(bool low);
+hipError_t launch_conv_small_full(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
+                                  hipStream_t st, int num_cus);
+hipError_t launch_conv_small_list(const ListInst &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus);
 
 // Fused programs (BI_PROG_*), one workgroup per instance of n32 words.
 size_t fused_lds_bytes(int program, uint32_t n32);

@@ -567,9 +567,7 @@ static hipError_t launch_mfma(const Src &src, uint32_t nmax, uint64_t count, hip
         case 1:
             // one-wave workgroups: registers for 4 per SIMD when LDS holds 16
             // per CU (3, sized the same way at 2^13 bits, measured slower)
-            if (mfma_layout((nmax + 7) & ~7u).total * 16 <= 160 * 1024)
-                return ((nmax + 7) & ~7u) <= 128 ? launch_nw<1, 4, Src, false, true>(src, nmax, count, st, num_cus)
-                                                 : launch_nw<1, 4>(src, nmax, count, st, num_cus);
+            if (mfma_layout((nmax + 7) & ~7u).total * 16 <= 160 * 1024) return launch_nw<1, 4>(src, nmax, count, st, num_cus);
             return launch_nw<1, 1>(src, nmax, count, st, num_cus);
         case 2: return launch_nw<2, 1>(src, nmax, count, st, num_cus);
         default: return launch_nw<4, 1>(src, nmax, count, st, num_cus);
@@ -579,6 +577,7 @@ static hipError_t launch_mfma(const Src &src, uint32_t nmax, uint64_t count, hip
 hipError_t launch_bigmul_mfma(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n32, uint64_t batch,
                               hipStream_t st, int num_cus) {
     if (batch == 0) return hipSuccess;
+    if (n32 <= conv_small_max(false)) return launch_conv_small_full(a, b, c, n32, batch, st, num_cus);
     const UniformInst src{a, b, c, n32, batch};
     // 1017-1024 limbs (eight supertiles, 128 digit blocks) and 505-512 limbs
     // (four supertiles, 64 digit blocks): the k-major order
@@ -589,6 +588,7 @@ hipError_t launch_bigmul_mfma(const uint32_t *a, const uint32_t *b, uint32_t *c,
 
 hipError_t launch_bigmul_mfma_list(const ListInst &src, uint32_t nmax, uint64_t count_max, hipStream_t st,
                                    int num_cus) {
+    if (nmax <= conv_small_max(false)) return launch_conv_small_list(src, nmax, count_max, st, num_cus);
     return launch_mfma(src, nmax, count_max, st, num_cus);
 }
 

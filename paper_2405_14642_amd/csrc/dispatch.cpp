@@ -55,19 +55,20 @@ size_t uniform_algo_scratch_bytes(int alg, uint32_t n32) {
 
 // Built-in per-class tables, as bi_autotune measured them on MI355X (one
 // GPU, a fresh context).  Uniform batches, each class at its largest size:
-// the VALU schoolbook up to 64 limbs (2^11 bits), the int8-MFMA schoolbook up
-// to 4096 limbs (2^17 bits), the two-prime NTT at 8192 limbs.  Ragged batches
+// the int8-MFMA schoolbook up to 4096 limbs (2^17 bits; 2^22 words of 4 / 16 /
+// 32 / 64 limbs take 117 / 35 / 20 / 22 us, the VALU schoolbook 430 / 140 / 95
+// / 74), the two-prime NTT at 8192 limbs.  Ragged batches
 // (sizes spread over each class): the same up to 4096 limbs, Karatsuba over
 // 8192 (its work follows each instance's size; an NTT's transform length is
 // the class's).  Also the VALU schedule (Q output words per lane, waves per
 // workgroup) per class.  bi_autotune re-measures and replaces them on the
 // device at hand.
 static void default_tune(Tune &t) {
-    static const int algo[kNumClasses] = {BI_MUL_SCHOOL_VALU, BI_MUL_SCHOOL_VALU, BI_MUL_SCHOOL_VALU,
+    static const int algo[kNumClasses] = {BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_NTT};
-    static const int list[kNumClasses] = {BI_MUL_SCHOOL_VALU, BI_MUL_SCHOOL_VALU, BI_MUL_SCHOOL_VALU,
+    static const int list[kNumClasses] = {BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_KARATSUBA};
