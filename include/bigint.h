@@ -25,7 +25,7 @@
  * are reported as BI_EHIP; asynchronous device faults surface at the caller's
  * next synchronisation.  bi_last_error() gives a message for the last failing
  * call on the calling host thread.  A context is not thread-safe: use one per
- * host thread or serialise calls.  bigmul (NTT and large-product MFMA paths),
+ * host thread or serialise calls.  bigmul (NTT and Karatsuba paths),
  * bigmul_v and bigadd_large use one scratch buffer owned by the context: such
  * calls on different streams of one context must not overlap in time (order
  * them with events, or use a context per stream).  When a call needs more
@@ -190,8 +190,7 @@ bi_status bigmul(bi_ctx *ctx, const void *a, const void *b, void *out,
  * bigmul_noalloc -- bigmul for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same products, bit-identical, with every scratch buffer
- * the kernels use (NTT transforms, the large-product MFMA slots, Karatsuba
- * levels) in one fixed device array of BI_NOALLOC_SCRATCH_BYTES per GPU that
+ * the kernels use (NTT transforms, Karatsuba levels) in one fixed device array of BI_NOALLOC_SCRATCH_BYTES per GPU that
  * is part of the library's code object and is held until the process ends.
  * The call makes no device allocation or free.  Batches whose scratch
  * exceeds the array run in rounds that fit it; BI_ESIZE if a single product

@@ -74,7 +74,6 @@ size_t batch_scratch_bytes(uint64_t count, int num_cus) {
 
 size_t list_algo_scratch_bytes(int alg, uint32_t nmax, uint64_t count) {
     switch (alg) {
-        case BI_MUL_SCHOOL_MFMA: return nmax <= mfma_max_limbs() ? 0 : ntt_list_scratch_bytes(count);
         case BI_MUL_NTT: return ntt_list_scratch_bytes(count);
         case BI_MUL_NTT_PF64: return ntt64_list_scratch_bytes(count);
         default: return 0;
@@ -84,11 +83,7 @@ size_t list_algo_scratch_bytes(int alg, uint32_t nmax, uint64_t count) {
 hipError_t launch_bigmul_list_algo(const Ctx &c, const Tune &tune, const ListInst &src, uint32_t nmax,
                                    uint64_t count_max, int alg, void *scr, size_t scr_bytes, hipStream_t st) {
     switch (alg) {
-        case BI_MUL_SCHOOL_MFMA:
-            return nmax <= mfma_max_limbs() ? launch_bigmul_mfma_list(src, nmax, count_max, st, c.num_cus)
-                                            : launch_bigmul_mfma_big_list(src, nmax, count_max,
-                                                                          static_cast<uint8_t *>(scr), scr_bytes, st,
-                                                                          c.num_cus);
+        case BI_MUL_SCHOOL_MFMA: return launch_bigmul_mfma_list(src, nmax, count_max, st, c.num_cus);
         case BI_MUL_NTT:
             return launch_bigmul_ntt_list(c.ntt.c, src, nmax, count_max, static_cast<uint32_t *>(scr), st, c.num_cus);
         case BI_MUL_NTT_PF64:

@@ -258,23 +258,15 @@ hipError_t launch_bigmul_ntt64_list(const NttConst64 &K, const ListInst &src, ui
                                     uint64_t *scratch, hipStream_t st, int num_cus);
 size_t ntt64_list_scratch_bytes(uint64_t count);
 
-// int8-MFMA schoolbook: one workgroup per product up to mfma_max_limbs()
-// 32-bit limbs; above that (up to kMaxLimbs32) the three-kernel large-product
-// path, with a scratch slot of mfma_big_slot_bytes(n) per product.
-uint32_t mfma_max_limbs();
-size_t mfma_big_slot_bytes(uint32_t nmax);
-hipError_t launch_bigmul_mfma_big(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n32, uint64_t batch,
-                                  uint8_t *scr, hipStream_t st, int num_cus, uint64_t round);
-hipError_t launch_bigmul_mfma_big_list(const ListInst &src, uint32_t nmax, uint64_t count_max, uint8_t *scr,
-                                       size_t scr_bytes, hipStream_t st, int num_cus);
+// int8-MFMA schoolbook (bi_conv.hpp), no scratch: products of up to 128 words
+// share wavefronts (conv_small.hip), larger ones take a workgroup each
+// (conv_wg.hip).
 hipError_t launch_bigmul_mfma(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n32, uint64_t batch,
                               hipStream_t st, int num_cus);
-
-// The same products of up to conv_small_max(low) words on 16 x 16 x 64 tiles
-// (bi_conv.hpp), one wavefront per row of products.
-uint32_t conv_small_max(bool low);
-hipError_t launch_conv_small_full(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
-                                  hipStream_t st, int num_cus);
+hipError_t launch_bigmul_mfma_list(const ListInst &src, uint32_t nmax, uint64_t count_max, hipStream_t st,
+                                   int num_cus);
+constexpr uint32_t kConvSmallMax = 128;
+hipError_t launch_conv_small_full(const UniformInst &src, hipStream_t st, int num_cus);
 hipError_t launch_conv_small_list(const ListInst &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus);
 
 // Fused programs (BI_PROG_*), one workgroup per instance of n32 words.

@@ -198,8 +198,6 @@ __global__ __launch_bounds__(256, MODE == kPoly ? 4 : MODE == kLow ? 5 : 6) void
     }
 }
 
-uint32_t conv_small_max(bool low) { return low ? 256 : 128; }
-
 template <int TPI, int MODE, class Src>
 static hipError_t launch_small(const Src &src, uint64_t count, hipStream_t st, int num_cus) {
     constexpr int IPW = 4 / TPI;
@@ -220,18 +218,19 @@ static hipError_t launch_small(const Src &src, uint64_t count, hipStream_t st, i
     return hipGetLastError();
 }
 
-hipError_t launch_conv_small_full(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
-                                  hipStream_t st, int num_cus) {
-    const UniformInst src{a, b, c, n, batch};
-    if (n <= 32) return launch_small<1, kFull>(src, batch, st, num_cus);
-    if (n <= 64) return launch_small<2, kFull>(src, batch, st, num_cus);
-    return launch_small<4, kFull>(src, batch, st, num_cus);
-}
-
-hipError_t launch_conv_small_list(const ListInst &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus) {
+template <class Src>
+static hipError_t launch_small_full(const Src &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus) {
     if (nmax <= 32) return launch_small<1, kFull>(src, count, st, num_cus);
     if (nmax <= 64) return launch_small<2, kFull>(src, count, st, num_cus);
     return launch_small<4, kFull>(src, count, st, num_cus);
+}
+
+hipError_t launch_conv_small_full(const UniformInst &src, hipStream_t st, int num_cus) {
+    return launch_small_full(src, src.n, src.batch, st, num_cus);
+}
+
+hipError_t launch_conv_small_list(const ListInst &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus) {
+    return launch_small_full(src, nmax, count, st, num_cus);
 }
 
 }  // namespace bi

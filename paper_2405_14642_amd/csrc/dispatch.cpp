@@ -46,7 +46,6 @@ int kara_base_algo(const Tune &tune, uint32_t h, bool ragged) {
 
 size_t uniform_algo_scratch_bytes(int alg, uint32_t n32) {
     switch (alg) {
-        case BI_MUL_SCHOOL_MFMA: return n32 <= mfma_max_limbs() ? 0 : mfma_big_slot_bytes(n32);
         case BI_MUL_NTT: return ntt_scratch_bytes(n32, 1);
         case BI_MUL_NTT_PF64: return ntt64_scratch_bytes(n32, 1);
         default: return 0;
@@ -199,13 +198,7 @@ bi_status dispatch_bigmul(Ctx &c, const void *a, const void *b, void *out, uint3
             e = launch_bigmul_valu(A, B, C, n32, batch, valu_plan_tuned(n32, c.tune), st, c.num_cus);
             break;
         case BI_MUL_SCHOOL_MFMA:
-            if (n32 <= mfma_max_limbs()) {
-                e = launch_bigmul_mfma(A, B, C, n32, batch, st, c.num_cus);
-            } else {
-                s = bigmul_scratch(c, mfma_big_slot_bytes(n32), batch, st, fixed, fixed_bytes, &scr, &round);
-                if (s != BI_OK) return s;
-                e = launch_bigmul_mfma_big(A, B, C, n32, batch, static_cast<uint8_t *>(scr), st, c.num_cus, round);
-            }
+            e = launch_bigmul_mfma(A, B, C, n32, batch, st, c.num_cus);
             break;
         case BI_MUL_NTT:
             if (ntt_log_len(n32) == 0) return set_error(BI_EALGO, "NTT supports up to %u limbs", kNttLmax / 4);

@@ -59,18 +59,44 @@ def test_small_full(B, ctx, orc, n, off):
         assert differing(G.from_dev(out, np.uint32), orc.mul(a, b)) == [], (n, off, batch)
 
 
-def test_small_ragged(B, ctx, orc):
-    """Every size up to 128 words in one batch, twice over and shuffled, so
-    that a wave meets longer and shorter instances in turn."""
-    n = np.random.default_rng(3).permutation(np.repeat(np.arange(1, 129), 2))
+# a workgroup of 1, 2, 4, 8 and 16 waves takes 256, 512, .. 4096 words, one of
+# 16 waves with two units each 8192; units are 256 words of an operand, bands
+# end at every multiple of 32 words; a chunk is 4 words
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("n", [129, 160, 161, 253, 255, 256, 257, 288, 289, 384, 480, 481, 511, 512, 513, 545, 767, 768, 769,
+                               992, 1021, 1024, 1025, 1057, 1536, 1537, 2016, 2047, 2048, 2049, 3073, 4064, 4093, 4096,
+                               4097, 6145, 8160, 8191, 8192])
+def test_workgroup_full(B, ctx, orc, n, off):
+    batch = 13 if n <= 1100 else 4
+    a, b = operands(n, batch, n)
+    out = G.empty_dev((batch * 2 * n + off,), np.uint32)[off:].reshape(batch, 2 * n)
+    B.bigmul(ctx, padded(a, off), padded(b, off), out, algo=MFMA)
+    G.sync()
+    assert differing(G.from_dev(out, np.uint32), orc.mul(a, b)) == []
+
+
+def test_workgroup_many(B, ctx, orc):
+    """More products than resident workgroups, so that each meets several."""
+    for n, batch in ((200, 9001), (300, 5003), (1000, 2501)):
+        a, b = operands(n, batch, n)
+        out = G.empty_dev((batch, 2 * n), np.uint32)
+        B.bigmul(ctx, G.to_dev(a), G.to_dev(b), out, algo=MFMA)
+        G.sync()
+        assert differing(G.from_dev(out, np.uint32), orc.mul(a, b)) == [], n
+
+
+@pytest.mark.parametrize("sizes", [np.arange(1, 129), np.r_[129:257:3, 257:513:7, 513:1025:19],
+                                   np.r_[1025:2049:101, 2049:4097:307, 4097:8193:1023]], ids=["small", "mid", "large"])
+def test_ragged(B, ctx, orc, sizes):
+    """Sizes of every class twice over and shuffled, so that a wave or a
+    workgroup meets longer and shorter instances in turn."""
+    n = np.random.default_rng(3).permutation(np.repeat(sizes, 2))
     off = np.concatenate([[0], np.cumsum(n)[:-1]])
-    a, b = (x[0] for x in operands(9, 1, int(n.sum())))
-    a, b = a.copy(), b.copy()
     rng = np.random.default_rng(4)
-    for i in range(0, len(n), 2):
-        sl = slice(off[i], off[i] + n[i])
-        a[sl] = rng.integers(0, 2**32, n[i], dtype=np.uint32)
-        b[sl] = rng.integers(0, 2**32, n[i], dtype=np.uint32)
+    a, b = (rng.integers(0, 2**32, int(n.sum()), dtype=np.uint32) for _ in range(2))
+    for i in range(0, len(n), 3):
+        a[off[i]:off[i] + n[i]] = 0xFFFFFFFF
+        b[off[i]:off[i] + n[i]] = 0xFFFFFFFF
     out = G.empty_dev((2 * a.size,), np.uint32)
     B.bigmul_v(ctx, G.to_dev(a), G.to_dev(b), out, G.desc_dev(off, off, 2 * off, n), len(n), 32, algo=MFMA)
     G.sync()
