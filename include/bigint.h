@@ -176,8 +176,8 @@ bi_status bigmul_large(bi_ctx *ctx, const void *a, const void *b, void *out, uin
  *                        padded length), recombined, then a carry scan.
  *   BI_MUL_KARATSUBA     levels of the subtractive Karatsuba split (a0 b0,
  *                        a1 b1 and |a0 - a1| |b0 - b1| for halves a0, a1,
- *                        b0, b1) until the operands have at most 1024 words
- *                        (2^15 bits), whose products run as one batch with
+ *                        b0, b1) until the operands have at most 1024 or 2048
+ *                        words (per size class), whose products run as one batch with
  *                        the tuned algorithm of that size; 3^levels base
  *                        products per pair instead of 4^levels.
  *   BI_MUL_AUTO          the tuned choice of the above for the size class.
@@ -325,7 +325,8 @@ bi_status bi_tune_set_list(bi_ctx *ctx, const int *algo_in, uint32_t n_in);
 
 /* The Karatsuba base per class: BI_MUL_KARATSUBA on class k's sizes splits
  * until the operands have at most base[k] 32-bit words (512, 1024 or 2048;
- * default 1024); bi_autotune picks it per class.  bi_tune_set_kara replaces
+ * default 1024, 2048 for the two largest classes); bi_autotune picks it per
+ * class.  bi_tune_set_kara replaces
  * entries 0 .. n_in-1 (BI_EINVAL, nothing changed, for any other value). */
 bi_status bi_tune_get_kara(const bi_ctx *ctx, uint32_t *base_out, uint32_t n_out);
 bi_status bi_tune_set_kara(bi_ctx *ctx, const uint32_t *base_in, uint32_t n_in);

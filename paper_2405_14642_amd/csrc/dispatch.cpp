@@ -56,17 +56,18 @@ size_t uniform_algo_scratch_bytes(int alg, uint32_t n32) {
 // GPU, a fresh context).  Uniform batches, each class at its largest size:
 // the int8-MFMA schoolbook up to 4096 limbs (2^17 bits; 2^22 words of 4 / 16 /
 // 32 / 64 limbs take 117 / 35 / 20 / 22 us, the VALU schoolbook 430 / 140 / 95
-// / 74), the two-prime NTT at 8192 limbs.  Ragged batches
-// (sizes spread over each class): the same up to 4096 limbs, Karatsuba over
-// 8192 (its work follows each instance's size; an NTT's transform length is
-// the class's).  Also the VALU schedule (Q output words per lane, waves per
+// / 74), Karatsuba at 8192 limbs (64 products: 63 us, the MFMA schoolbook 138,
+// the two-prime NTT 78; 6000 limbs: 53 / 80 / 74).  Ragged batches (sizes
+// spread over each class): the same.  Karatsuba's base is 2048 limbs in the
+// two largest classes (8192 x 64: 62.7 us, 66.2 over 1024; 4096 x 256: 56.8,
+// 63.6), 1024 below.  Also the VALU schedule (Q output words per lane, waves per
 // workgroup) per class.  bi_autotune re-measures and replaces them on the
 // device at hand.
 static void default_tune(Tune &t) {
     static const int algo[kNumClasses] = {BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
-                                          BI_MUL_NTT};
+                                          BI_MUL_KARATSUBA};
     static const int list[kNumClasses] = {BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
                                           BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA, BI_MUL_SCHOOL_MFMA,
@@ -78,7 +79,7 @@ static void default_tune(Tune &t) {
         t.list_algo[k] = list[k];
         t.valu_q[k] = q[k];
         t.valu_nw[k] = nw[k];
-        t.kara_base[k] = kKaraBase;
+        t.kara_base[k] = uint16_t(class_nmax(k) > 2048 ? 2 * kKaraBase : kKaraBase);
     }
 }
 
