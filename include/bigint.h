@@ -225,8 +225,8 @@ bi_status bi_mul_plan(const bi_ctx *ctx, uint32_t n_limbs, uint32_t limb_bits, i
 
 /*
  * bi_fused -- the paper's fused programs (Section 6.1): several same-length
- * operations per instance in one kernel, each instance in one workgroup with
- * its intermediates in LDS (operands read once, the result written once).
+ * operations per instance in one kernel, its intermediates in registers and
+ * LDS (operands read once, the result written once).
  * All arithmetic is mod 2^(n_limbs * limb_bits), as the paper's add and its
  * same-length product (the low n limbs of eq. (1)):
  *   BI_PROG_ADD6  six additions in a chain, a + b, then + a, + b, + a, + b,

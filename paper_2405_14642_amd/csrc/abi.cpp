@@ -298,8 +298,6 @@ bi_status bi_fused(bi_ctx *ctx, int program, const void *a, const void *b, void 
     if (overlaps(out, tot, a, tot) || overlaps(out, tot, b, tot)) return fail(BI_EALIAS, "out overlaps an input");
     if (!ctx) return fail(BI_EINVAL, "ctx is NULL");
     const uint32_t n32 = n_limbs * (limb_bits / 32);
-    if (bi::fused_lds_bytes(program, n32) > 160 * 1024)
-        return fail(BI_ESIZE, "program %d does not fit one workgroup's LDS at %u words", program, n32);
     DeviceGuard g(ctx->device);
     if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
     const hipError_t e = bi::launch_fused(program, static_cast<const uint32_t *>(a), static_cast<const uint32_t *>(b),

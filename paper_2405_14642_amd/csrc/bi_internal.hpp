@@ -269,8 +269,14 @@ constexpr uint32_t kConvSmallMax = 128;
 hipError_t launch_conv_small_full(const UniformInst &src, hipStream_t st, int num_cus);
 hipError_t launch_conv_small_list(const ListInst &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus);
 
-// Fused programs (BI_PROG_*), one workgroup per instance of n32 words.
-size_t fused_lds_bytes(int program, uint32_t n32);
+// Low product (mod 2^N) or (poly) the polynomial program of n-word instances
+// on the same kernels.
+hipError_t launch_conv_fused(bool poly, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
+                             hipStream_t st, int num_cus);
+constexpr uint32_t kConvSmallLowMax = 256;
+hipError_t launch_conv_small_low(bool poly, const LowInst &src, hipStream_t st, int num_cus);
+
+// Fused programs (BI_PROG_*).
 hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n32, uint64_t batch,
                         hipStream_t st, int num_cus);
 

@@ -233,4 +233,14 @@ hipError_t launch_conv_small_list(const ListInst &src, uint32_t nmax, uint64_t c
     return launch_small_full(src, nmax, count, st, num_cus);
 }
 
+hipError_t launch_conv_small_low(bool poly, const LowInst &src, hipStream_t st, int num_cus) {
+    const uint32_t n = src.u.n;
+    const uint64_t batch = src.u.batch;
+#define BI_SMALL(T) poly ? launch_small<T, kPoly>(src, batch, st, num_cus) : launch_small<T, kLow>(src, batch, st, num_cus)
+    if (n <= 64) return BI_SMALL(1);
+    if (n <= 128) return BI_SMALL(2);
+    return BI_SMALL(4);
+#undef BI_SMALL
+}
+
 }  // namespace bi

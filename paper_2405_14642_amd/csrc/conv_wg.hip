@@ -19,7 +19,10 @@
 // it (32 x 32 x 32 tiles over 8-byte windows of a in LDS; three kernels and
 // global scratch above 1024 words): 4096 x 1024 words 81.4 -> 62.1 us (2.2e15
 // int8 ops/s), 8192 x 512 words 61.7 -> 40.7, 16384 x 256 words 51.9 -> 24.5,
-// 2048 x 2048 words 198 -> 102, 512 x 4096 words 196 -> 91 us.
+// 2048 x 2048 words 198 -> 102, 512 x 4096 words 196 -> 91 us.  Low products
+// and Poly against the VALU schoolbook in LDS: 16384 x 512 words 266 -> 40.5
+// us, 4096 x 2048 words (Poly) 3041 -> 408, 128 x 8192 words 657 -> 78 and
+// (Poly) 2631 -> 303.
 #include <algorithm>
 #include <atomic>
 
@@ -457,6 +460,23 @@ hipError_t launch_bigmul_mfma_list(const ListInst &src, uint32_t nmax, uint64_t 
     if (nmax > kMaxLimbs32) return hipErrorInvalidValue;
     if (nmax <= kConvSmallMax) return launch_conv_small_list(src, nmax, count_max, st, num_cus);
     return launch_full(src, nmax, count_max, st, num_cus);
+}
+
+hipError_t launch_conv_fused(bool poly, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
+                             hipStream_t st, int num_cus) {
+    if (batch == 0) return hipSuccess;
+    if (n > kMaxLimbs32) return hipErrorInvalidValue;
+    const LowInst src{{a, b, c, n, batch}};
+    if (n <= kConvSmallLowMax) return launch_conv_small_low(poly, src, st, num_cus);
+#define BI_WG(W)                                              \
+    poly ? launch_wg<W, 1, kPoly>(src, n, batch, st, num_cus) \
+         : launch_wg<W, 1, kLow>(src, n, batch, st, num_cus)
+    if (n <= 512) return BI_WG(1);
+    if (n <= 1024) return BI_WG(2);
+    if (n <= 2048) return BI_WG(4);
+    if (n <= 4096) return BI_WG(8);
+    return BI_WG(16);
+#undef BI_WG
 }
 
 }  // namespace bi

@@ -1,6 +1,6 @@
 // Fused multi-operation programs (Section 6.1): several same-length
-// operations on one instance inside one workgroup, the intermediates kept in
-// LDS, the operands read from HBM once and the result written once.
+// operations per instance in one kernel, the intermediates kept in registers
+// and LDS, the operands read from HBM once and the result written once.
 //
 //   BI_PROG_ADD6  six additions, a + b, then + a, + b, + a, + b, + a in turn:
 //                 4 a + 3 b mod 2^N (the paper names only "six additions";
@@ -15,179 +15,30 @@
 // to 256 words are packed several to a wave (a segmented ballot-adder: the
 // last chunk of an instance neither generates nor propagates into the next),
 // larger ones take a workgroup whose waves exchange one carry summary per
-// addition.  In Poly every addition is a workgroup ballot-adder pass
-// (Section 2) from LDS to LDS.
-// A same-length product is the VALU schoolbook of Section 3 restricted to the
-// output words below n: waves take blocks of 64 Q consecutive coefficients in
-// a snake order (cost grows with the block index), the factor read uniformly
-// from LDS is the scalar operand of v_mad_u64_u32 and the other factor is read
-// as a sliding window from a zero-padded LDS buffer; each lane folds its Q
-// (accumulator, overflow count) pairs into Q low words (written to the result
-// buffer) and a (high, carry) pair, and a ballot-adder pass adds the pairs in
-// place.  Words at or above n are dropped: arithmetic is mod 2^N.
-// Products and Poly of up to 256 words instead run several instances per
-// wavefront (fused_packed_kernel): an instance takes a segment of lanes, its
-// operands sit in the wavefront's own LDS areas (the per-lane factor is then
-// a VGPR operand), the (high, carry) pair moves to the next lane by a lane
-// shuffle and the segment's chunks are added with one ballot-adder step, so
-// Poly's intermediates stay in registers but for the two factors of its last
-// product.
+// addition.
+//
+// Products and Poly above 32 words run on the matrix cores (launch_conv_fused).
+// Shorter instances share wavefronts on the VALU (fused_packed_kernel): an
+// instance takes a segment of lanes, its operands sit in the wavefront's own
+// LDS areas and each lane accumulates its output words over a sliding window
+// (Section 3), the (high, carry) pair moves to the next lane by a lane shuffle
+// and the segment's chunks are added with one ballot-adder step, so Poly's
+// intermediates stay in registers but for the two factors of its last product.
 #include <algorithm>
 #include <atomic>
 
 #include "bi_common.hpp"
 #include "bi_internal.hpp"
 #include "bi_valu.hpp"
-#include "bi_wgadd.hpp"
 
 namespace bi {
 
-// Longest instance (32-bit words) of the packed product / Poly kernels.
-constexpr uint32_t kPackedMaxWords = 256;
+// Longest instance (32-bit words) of the packed product / Poly kernels, and
+// output words per lane.
+constexpr uint32_t kPackedMaxWords = 32;
+constexpr int kPackedQ = 2;
 
 namespace {
-
-// Zero words on each side of a buffer used as the windowed factor of a
-// product: a block spans 64 Q coefficients and its step loop runs in groups
-// of 4, so the window reaches 64 Q + 3 words below 0 and 64 Q words above n.
-template <int Q> constexpr uint32_t fused_pad() { return 64 * Q + 4; }
-
-// x = X + Y over n words, in place in LDS.
-struct AddSrc {
-    const uint32_t *X, *Y;
-    uint32_t n;
-    __device__ __forceinline__ void operator()(uint32_t c, uint32_t (&x)[4], uint32_t (&y)[4]) const {
-        const uint4 u = *reinterpret_cast<const uint4 *>(X + 4 * c);
-        const uint4 v = *reinterpret_cast<const uint4 *>(Y + 4 * c);
-        x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w;
-        y[0] = v.x; y[1] = v.y; y[2] = v.z; y[3] = v.w;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (4 * c + t >= n) { x[t] = 0; y[t] = 0; }
-    }
-};
-
-struct LdsSink {
-    uint32_t *Z;
-    uint32_t n;
-    __device__ __forceinline__ void operator()(uint32_t c, const uint32_t (&s)[4]) const {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (4 * c + t < n) Z[4 * c + t] = s[t];
-    }
-};
-
-template <int NW>
-__device__ __forceinline__ void wg_add_lds(uint32_t *Z, const uint32_t *X, const uint32_t *Y, uint32_t n,
-                                           uint32_t *summary) {
-    (void)wg_add_rows_sink<NW>(AddSrc{X, Y, n}, LdsSink{Z, n}, n, summary);
-    __syncthreads();
-}
-
-// Low n words of the (Q low words, high / carry pair) per lane group: H of
-// group g belongs at words Q (g + 1) and Q (g + 1) + 1.
-template <int Q>
-struct MulLowSrc {
-    const uint32_t *L;
-    const uint2 *H;
-    uint32_t n;
-    __device__ __forceinline__ void operator()(uint32_t c, uint32_t (&x)[4], uint32_t (&y)[4]) const {
-        const uint4 l = *reinterpret_cast<const uint4 *>(L + 4 * c);
-        x[0] = l.x; x[1] = l.y; x[2] = l.z; x[3] = l.w;
-        if constexpr (Q == 4) {
-            if (c >= 1) {
-                const uint2 h = H[c - 1];
-                y[0] = h.x; y[1] = h.y;
-            }
-        } else {
-            if (c >= 1) {
-                const uint2 h = H[2 * c - 1];
-                y[0] = h.x; y[1] = h.y;
-            }
-            const uint2 h2 = H[2 * c];
-            y[2] = h2.x; y[3] = h2.y;
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (4 * c + t >= n) { x[t] = 0; y[t] = 0; }
-    }
-};
-
-// Z = (U V) mod 2^(32 n).  U: read uniformly, words up to n + 2 (zero above
-// n); V: zero at least fused_pad<Q>() words on each side; Z: n words (may not
-// alias U or V); H: scratch of 64 entries per block.
-template <int Q, int NW>
-__device__ __forceinline__ void wg_mul_low(uint32_t *Z, const uint32_t *U, const uint32_t *V, uint2 *H, uint32_t n,
-                                           uint32_t *summary) {
-    constexpr uint32_t span = 64 * Q;
-    const uint32_t lane = lane_id(), wave = wave_in_block();
-    const uint32_t NB = (n + span - 1) / span;
-    for (uint32_t r = 0;; ++r) {
-        const uint32_t slot = (r & 1u) ? (NW - 1 - wave) : wave;  // snake over rising block costs
-        const uint32_t blk = r * NW + slot;
-        if (blk >= NB) break;
-        const uint32_t k0 = blk * span, kl = k0 + Q * lane;
-        const uint32_t ihi = min(k0 + span - 1, n - 1);  // steps i <= k for every coefficient k of the block
-        uint64_t acc[Q];
-        uint32_t cnt[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) { acc[q] = 0; cnt[q] = 0; }
-        // window w[q] = V[kl + q - i] at the current step i
-        uint32_t w[4];
-        auto window = [&](int32_t at, uint32_t (&x)[4]) {
-            if constexpr (Q == 4) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(V + at);
-                x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-            } else {
-                const uint2 v0 = *reinterpret_cast<const uint2 *>(V + at);
-                const uint2 v1 = *reinterpret_cast<const uint2 *>(V + at + 2);
-                x[0] = v0.x; x[1] = v0.y; x[2] = v1.x; x[3] = v1.y;
-            }
-        };
-        window(int32_t(kl), w);
-        for (uint32_t i = 0; i <= ihi; i += 4) {
-            uint32_t x[4];  // V[kl - i - 4 .. kl - i - 1]
-            window(int32_t(kl) - int32_t(i) - 4, x);
-            uint32_t av[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) av[u] = __builtin_amdgcn_readfirstlane(U[i + u]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    const int t = q - u + 4;
-                    mac(acc[q], cnt[q], av[u], t >= 4 ? w[t - 4] : x[t]);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) w[q] = x[q];
-        }
-        // position p collects lo(acc[p]) + hi(acc[p-1]) + cnt[p-2] and the running carry
-        uint32_t R[Q + 2];
-        uint64_t carry = 0;
-#pragma unroll
-        for (int p = 0; p < Q + 2; ++p) {
-            uint64_t s = carry;
-            if (p < Q) s += uint32_t(acc[p]);
-            if (p >= 1 && p <= Q) s += uint32_t(acc[p - 1] >> 32);
-            if (p >= 2) s += cnt[p - 2];
-            R[p] = uint32_t(s);
-            carry = s >> 32;
-        }
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (kl + q < n) Z[kl + q] = R[q];
-        H[blk * 64 + lane] = make_uint2(R[Q], R[Q + 1]);
-    }
-    __syncthreads();
-    // Z = L + H in place: each chunk is read and written by the same lane
-    (void)wg_add_rows_sink<NW>(MulLowSrc<Q>{Z, H, n}, LdsSink{Z, n}, n, summary);
-    __syncthreads();
-}
-
-__device__ __forceinline__ void load_operand(uint32_t *dst, const uint32_t *src, uint32_t n) {
-    for (uint32_t t = threadIdx.x; t < n; t += blockDim.x) dst[t] = src[t];
-}
 
 // A lane's 4-word chunk c of an n-word operand (zero past n or when invalid).
 __device__ __forceinline__ void load_chunk(const uint32_t *p, uint32_t n, uint32_t c, bool valid, uint32_t (&x)[4]) {
@@ -325,80 +176,6 @@ __global__ __launch_bounds__(64 * NW) void fused_add6_rows_kernel(const uint32_t
     }
 }
 
-// LDS of the polynomial program: four padded buffers (a, b and two
-// intermediates at most are live at once) and the products' H scratch.
-struct PolyLayout {
-    uint32_t stride, pad, h_off, sum_off, words;
-};
-
-static PolyLayout poly_layout(uint32_t n, int Q, int NW) {
-    PolyLayout l;
-    l.pad = 64 * Q + 4;
-    l.stride = ((n + 3) & ~3u) + 2 * l.pad;
-    const uint32_t NB = (n + 64 * Q - 1) / (64 * Q);
-    l.h_off = 4 * l.stride;
-    l.sum_off = l.h_off + 2 * NB * 64;
-    l.words = l.sum_off + NW;
-    return l;
-}
-
-template <int Q, int NW>
-__global__ __launch_bounds__(64 * NW) void fused_poly_kernel(const uint32_t *__restrict__ a,
-                                                             const uint32_t *__restrict__ b, uint32_t *__restrict__ out,
-                                                             uint32_t n, uint64_t batch) {
-    extern __shared__ __align__(16) uint32_t lds[];
-    constexpr uint32_t pad = fused_pad<Q>();
-    const uint32_t stride = ((n + 3) & ~3u) + 2 * pad;
-    const uint32_t NB = (n + 64 * Q - 1) / (64 * Q);
-    uint32_t *buf[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) buf[k] = lds + k * stride + pad;
-    uint2 *H = reinterpret_cast<uint2 *>(lds + 4 * stride);
-    uint32_t *summary = lds + 4 * stride + 2 * NB * 64;
-    // pads and tails are zero for the whole launch: results only write [0, n)
-    for (uint32_t t = threadIdx.x; t < 4 * stride; t += 64 * NW) lds[t] = 0;
-    __syncthreads();
-    for (uint64_t q = blockIdx.x; q < batch; q += gridDim.x) {
-        uint32_t *A = buf[0], *B = buf[1], *Z1 = buf[2], *Z2 = buf[3];
-        load_operand(A, a + q * n, n);
-        load_operand(B, b + q * n, n);
-        __syncthreads();
-        wg_mul_low<Q, NW>(Z1, A, B, H, n, summary);  // a b
-        wg_mul_low<Q, NW>(Z2, A, A, H, n, summary);  // a a
-        wg_add_lds<NW>(Z2, Z2, B, n, summary);        // a a + b
-        wg_mul_low<Q, NW>(A, B, B, H, n, summary);    // b b (a is no longer needed)
-        wg_add_lds<NW>(A, A, B, n, summary);          // b b + b
-        wg_mul_low<Q, NW>(B, Z2, A, H, n, summary);   // (a a + b)(b b + b)
-        wg_add_rows<NW>(AddSrc{B, Z1, n}, out + q * n, n, summary);
-        __syncthreads();
-    }
-}
-
-// Same-length product alone: a and b in two padded buffers, the result
-// formed in a third and copied out.
-template <int Q, int NW>
-__global__ __launch_bounds__(64 * NW) void fused_mullow_kernel(const uint32_t *__restrict__ a,
-                                                               const uint32_t *__restrict__ b,
-                                                               uint32_t *__restrict__ out, uint32_t n, uint64_t batch) {
-    extern __shared__ __align__(16) uint32_t lds[];
-    constexpr uint32_t pad = fused_pad<Q>();
-    const uint32_t stride = ((n + 3) & ~3u) + 2 * pad;
-    const uint32_t NB = (n + 64 * Q - 1) / (64 * Q);
-    uint32_t *U = lds + pad, *V = U + stride, *Z = V + stride;
-    uint2 *H = reinterpret_cast<uint2 *>(lds + 3 * stride);
-    uint32_t *summary = lds + 3 * stride + 2 * NB * 64;
-    for (uint32_t t = threadIdx.x; t < 3 * stride; t += 64 * NW) lds[t] = 0;
-    __syncthreads();
-    for (uint64_t q = blockIdx.x; q < batch; q += gridDim.x) {
-        load_operand(U, a + q * n, n);
-        load_operand(V, b + q * n, n);
-        __syncthreads();
-        wg_mul_low<Q, NW>(Z, U, V, H, n, summary);
-        for (uint32_t t = threadIdx.x; t < n; t += 64 * NW) out[q * n + t] = Z[t];
-        __syncthreads();
-    }
-}
-
 namespace {
 
 // ---- Packed small instances (n <= 64 Q words): several per wavefront ----
@@ -422,17 +199,11 @@ __device__ __forceinline__ void seg_add(uint32_t (&x)[Q], const uint32_t (&y)[Q]
     for (int q = 0; q < Q; ++q) x[q] = s[q];
 }
 
-// Four words of V from `at` (16- or two 8-byte LDS reads).
-template <int Q>
+// Four words of V from `at`.
 __device__ __forceinline__ void seg_window(const uint32_t *V, int32_t at, uint32_t (&x)[4]) {
-    if constexpr (Q == 4) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(V + at);
-        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    } else {
-        const uint2 v0 = *reinterpret_cast<const uint2 *>(V + at);
-        const uint2 v1 = *reinterpret_cast<const uint2 *>(V + at + 2);
-        x[0] = v0.x; x[1] = v0.y; x[2] = v1.x; x[3] = v1.y;
-    }
+    const uint2 v0 = *reinterpret_cast<const uint2 *>(V + at);
+    const uint2 v1 = *reinterpret_cast<const uint2 *>(V + at + 2);
+    x[0] = v0.x; x[1] = v0.y; x[2] = v1.x; x[3] = v1.y;
 }
 
 // Z = this lane's chunk of (U V) mod 2^(32 n), U and V the LDS areas of the
@@ -449,10 +220,10 @@ __device__ __forceinline__ void seg_mul_low(const uint32_t *U, const uint32_t *V
 #pragma unroll
     for (int q = 0; q < Q; ++q) { acc[q] = 0; cnt[q] = 0; }
     uint32_t w[4];  // V[kl .. kl + 3]
-    seg_window<Q>(V, int32_t(kl), w);
+    seg_window(V, int32_t(kl), w);
     for (uint32_t i = 0; i < n; i += 4) {
         uint32_t x[4];  // V[kl - i - 4 .. kl - i - 1]
-        seg_window<Q>(V, int32_t(kl) - int32_t(i) - 4, x);
+        seg_window(V, int32_t(kl) - int32_t(i) - 4, x);
         const uint4 a4 = *reinterpret_cast<const uint4 *>(U + i);
         const uint32_t av[4] = {a4.x, a4.y, a4.z, a4.w};
 #pragma unroll
@@ -512,11 +283,12 @@ __host__ __device__ inline uint32_t packed_area(uint32_t n, uint32_t sq) { retur
 // wavefront per workgroup.  LDS: per instance 2 (product) or 4 (Poly)
 // operand areas.  Poly keeps a b in registers, forms a a + b and b b + b in
 // registers and stores them as the operands of the last product.
-template <int Q, int PROG>
+template <int PROG>
 __global__ __launch_bounds__(64) void fused_packed_kernel(const uint32_t *__restrict__ a,
                                                           const uint32_t *__restrict__ b, uint32_t *__restrict__ out,
                                                           uint32_t n, uint64_t batch, uint32_t seg_log) {
     extern __shared__ __align__(16) uint32_t lds[];
+    constexpr int Q = kPackedQ;
     constexpr uint32_t NA = PROG == BI_PROG_POLY ? 4 : 2;
     const uint32_t lane = lane_id(), S = 1u << seg_log, ipw = 64u >> seg_log;
     const uint32_t j = lane & (S - 1u), slot = lane >> seg_log;
@@ -559,78 +331,39 @@ __global__ __launch_bounds__(64) void fused_packed_kernel(const uint32_t *__rest
 
 namespace {
 
-// Packed path parameters for n words: (Q, seg_log), Q = 0 when n is too long.
-struct PackedPlan {
-    int Q = 0;
+// log2 of the lanes an instance of n words takes.
+uint32_t packed_seg_log(uint32_t n) {
+    const uint32_t lanes = (n + kPackedQ - 1) / kPackedQ;
     uint32_t seg_log = 0;
-};
-PackedPlan packed_plan(uint32_t n) {
-    PackedPlan p;
-    if (n == 0 || n > kPackedMaxWords) return p;
-    p.Q = n <= 64 ? 2 : 4;  // 2 measured faster at 32 words (Poly 1.58 vs 1.87 ms), 4 at 128
-    const uint32_t lanes = (n + p.Q - 1) / p.Q;
-    while ((1u << p.seg_log) < lanes) ++p.seg_log;
-    return p;
+    while ((1u << seg_log) < lanes) ++seg_log;
+    return seg_log;
 }
-size_t packed_lds_bytes(int program, uint32_t n, const PackedPlan &p) {
-    const uint32_t S = 1u << p.seg_log;
-    return 4ull * (64u >> p.seg_log) * (program == BI_PROG_POLY ? 4 : 2) * packed_area(n, S * uint32_t(p.Q));
-}
-
-// Waves per workgroup for n words: enough 64-chunk rows (six additions) or
-// block pairs (products) to give each wave work, a power of two up to 16.
-uint32_t pow2_waves(uint32_t units) {
-    return units >= 16 ? 16 : units >= 8 ? 8 : units >= 4 ? 4 : units >= 2 ? 2 : 1;
+size_t packed_lds_bytes(bool poly, uint32_t n, uint32_t seg_log) {
+    return 4ull * (64u >> seg_log) * (poly ? 4 : 2) * packed_area(n, kPackedQ << seg_log);
 }
 
 // Persistent grid of resident workgroups (each loops over instances).  One
 // instantiation per kernel, so each keeps its own occupancy record.
 using FusedKernel = void (*)(const uint32_t *, const uint32_t *, uint32_t *, uint32_t, uint64_t);
 template <FusedKernel kernel>
-hipError_t launch_persistent(uint32_t threads, size_t lds, const uint32_t *a, const uint32_t *b, uint32_t *c,
-                             uint32_t n, uint64_t batch, hipStream_t st, int num_cus) {
-    const void *fn = reinterpret_cast<const void *>(kernel);
-    // ((LDS bytes + 1) << 32 | resident workgroups per CU) of the last launch
-    // of this kernel (0: none yet)
-    static std::atomic<uint64_t> occ{0}, lds_set{0};
-    hipError_t e = hipSuccess;
-    if (lds > 0) {  // kernels with dynamic LDS may use all of a CU's
-        e = lds_limit_once(fn, lds_set);
+hipError_t launch_persistent(uint32_t threads, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n,
+                             uint64_t batch, hipStream_t st, int num_cus) {
+    static std::atomic<int> occ{0};  // resident workgroups per CU (0: not asked yet)
+    int o = occ.load(std::memory_order_relaxed);
+    if (o == 0) {
+        const hipError_t e =
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(kernel), int(threads), 0);
         if (e != hipSuccess) return e;
-    }
-    uint64_t o = occ.load(std::memory_order_relaxed);
-    if ((o >> 32) != lds + 1) {
-        int nblk = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nblk, fn, int(threads), lds);
-        if (e != hipSuccess) return e;
-        o = (uint64_t(lds + 1) << 32) | uint32_t(nblk < 1 ? 1 : nblk);
+        if (o < 1) o = 1;
         occ.store(o, std::memory_order_relaxed);
     }
-    const uint64_t cap = uint64_t(uint32_t(o)) * uint64_t(num_cus > 0 ? num_cus : 1);
+    const uint64_t cap = uint64_t(o) * uint64_t(num_cus > 0 ? num_cus : 1);
     const uint32_t grid = uint32_t(batch < cap ? batch : cap);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, st, a, b, c, n, batch);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, a, b, c, n, batch);
     return hipGetLastError();
 }
 
 }  // namespace
-
-// LDS words of the same-length product: three padded buffers, H, summary.
-static uint32_t mullow_lds_words(uint32_t n, int Q, int NW) {
-    const uint32_t stride = ((n + 3) & ~3u) + 2 * (64 * Q + 4);
-    const uint32_t NB = (n + 64 * Q - 1) / (64 * Q);
-    return 3 * stride + 2 * NB * 64 + NW;
-}
-
-size_t fused_lds_bytes(int program, uint32_t n32) {
-    if (program == BI_PROG_ADD6) return 0;  // registers only
-    const PackedPlan pp = packed_plan(n32);
-    if (pp.Q != 0) return packed_lds_bytes(program, n32, pp);
-    const int Q = n32 > 4096 ? 4 : 2;
-    const uint32_t NB = (n32 + 64 * Q - 1) / (64 * Q);
-    const int nw = int(pow2_waves((NB + 1) / 2));
-    if (program == BI_PROG_MUL_LOW) return 4ull * mullow_lds_words(n32, Q, nw);
-    return 4ull * poly_layout(n32, Q, nw).words;
-}
 
 hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
                         hipStream_t st, int num_cus) {
@@ -652,49 +385,28 @@ hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint3
         while (4 * nw < rows) nw *= 2;
         const uint32_t r = (rows + nw - 1) / nw;
 #define BI_ADD6_CASE(W, RR) \
-    if (nw == W && r == RR) return launch_persistent<&fused_add6_rows_kernel<W, RR>>(64 * W, 0, a, b, c, n, batch, st, num_cus);
+    if (nw == W && r == RR) return launch_persistent<&fused_add6_rows_kernel<W, RR>>(64 * W, a, b, c, n, batch, st, num_cus);
         BI_ADD6_CASE(1, 2) BI_ADD6_CASE(1, 3) BI_ADD6_CASE(1, 4) BI_ADD6_CASE(2, 3) BI_ADD6_CASE(2, 4)
         BI_ADD6_CASE(4, 3) BI_ADD6_CASE(4, 4) BI_ADD6_CASE(8, 3) BI_ADD6_CASE(8, 4)
 #undef BI_ADD6_CASE
         return hipErrorInvalidValue;
     }
-    const PackedPlan pp = packed_plan(n);
-    if (pp.Q != 0) {
-        const size_t lds = packed_lds_bytes(program, n, pp);
-        const uint64_t waves = (batch + (64u >> pp.seg_log) - 1) / (64u >> pp.seg_log);
-        const uint32_t grid = uint32_t(std::min<uint64_t>(waves, uint64_t(num_cus > 0 ? num_cus : 1) * 32));
-#define BI_PACKED_CASE(QQ, PR)                                                                                      \
-    if (pp.Q == QQ && program == PR) {                                                                              \
-        hipLaunchKernelGGL((fused_packed_kernel<QQ, PR>), dim3(grid), dim3(64), lds, st, a, b, c, n, batch,         \
-                           pp.seg_log);                                                                             \
-        return hipGetLastError();                                                                                   \
-    }
-        BI_PACKED_CASE(2, BI_PROG_MUL_LOW) BI_PACKED_CASE(4, BI_PROG_MUL_LOW)
-        BI_PACKED_CASE(2, BI_PROG_POLY) BI_PACKED_CASE(4, BI_PROG_POLY)
-#undef BI_PACKED_CASE
-        return hipErrorInvalidValue;
-    }
-    const int Q = n > 4096 ? 4 : 2;
-    const uint32_t NB = (n + 64 * Q - 1) / (64 * Q);
-    const uint32_t nw = pow2_waves((NB + 1) / 2);
-    if (program == BI_PROG_MUL_LOW) {
-        const size_t lds = 4ull * mullow_lds_words(n, Q, int(nw));
-#define BI_MULLOW_CASE(QQ, W)                                                                                       \
-    if (Q == QQ && nw == W)                                                                                         \
-        return launch_persistent<&fused_mullow_kernel<QQ, W>>(64 * W, lds, a, b, c, n, batch, st, num_cus);
-        BI_MULLOW_CASE(2, 1) BI_MULLOW_CASE(2, 2) BI_MULLOW_CASE(2, 4) BI_MULLOW_CASE(2, 8) BI_MULLOW_CASE(2, 16)
-        BI_MULLOW_CASE(4, 1) BI_MULLOW_CASE(4, 2) BI_MULLOW_CASE(4, 4) BI_MULLOW_CASE(4, 8) BI_MULLOW_CASE(4, 16)
-#undef BI_MULLOW_CASE
-        return hipErrorInvalidValue;
-    }
-    const size_t lds = 4ull * poly_layout(n, Q, int(nw)).words;
-#define BI_POLY_CASE(QQ, W)                                                                                         \
-    if (Q == QQ && nw == W)                                                                                         \
-        return launch_persistent<&fused_poly_kernel<QQ, W>>(64 * W, lds, a, b, c, n, batch, st, num_cus);
-    BI_POLY_CASE(2, 1) BI_POLY_CASE(2, 2) BI_POLY_CASE(2, 4) BI_POLY_CASE(2, 8) BI_POLY_CASE(2, 16)
-    BI_POLY_CASE(4, 1) BI_POLY_CASE(4, 2) BI_POLY_CASE(4, 4) BI_POLY_CASE(4, 8) BI_POLY_CASE(4, 16)
-#undef BI_POLY_CASE
-    return hipErrorInvalidValue;
+    const bool poly = program == BI_PROG_POLY;
+    // Small instances: the VALU schoolbook packed several to a wavefront is
+    // faster up to 32 words (2^22 words of 16 / 32 / 33 words, low product:
+    // 13.3 / 18.0 / 32.0 us against 47.5 / 27.0 / 26.0 on the matrix cores,
+    // whose tiles hold 64 words; Poly 51 / 55 / 107 against 161 / 85 / 84).
+    if (n > kPackedMaxWords) return launch_conv_fused(poly, a, b, c, n, batch, st, num_cus);
+    const uint32_t seg_log = packed_seg_log(n);
+    const size_t lds = packed_lds_bytes(poly, n, seg_log);
+    const uint64_t waves = (batch + (64u >> seg_log) - 1) / (64u >> seg_log);
+    const uint32_t grid = uint32_t(std::min<uint64_t>(waves, uint64_t(num_cus > 0 ? num_cus : 1) * 32));
+    if (poly)
+        hipLaunchKernelGGL((fused_packed_kernel<BI_PROG_POLY>), dim3(grid), dim3(64), lds, st, a, b, c, n, batch, seg_log);
+    else
+        hipLaunchKernelGGL((fused_packed_kernel<BI_PROG_MUL_LOW>), dim3(grid), dim3(64), lds, st, a, b, c, n, batch,
+                           seg_log);
+    return hipGetLastError();
 }
 
 }  // namespace bi

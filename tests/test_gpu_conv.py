@@ -104,3 +104,23 @@ def test_ragged(B, ctx, orc, sizes):
     for o, k in zip(off, n):
         exp = orc.mul(a[None, o:o + k], b[None, o:o + k])[0]
         assert (got[2 * o:2 * (o + k)] == exp).all(), int(k)
+
+
+PROG_POLY, PROG_MUL_LOW = 2, 3
+
+
+# tiles hold 64, 128 and 256 words of a low product's operand; one wave takes
+# 512 words, workgroups of 2, 4, 8 and 16 waves 1024 .. 8192; instances of up
+# to 32 words run elsewhere
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("n", [32, 33, 61, 64, 65, 127, 128, 129, 197, 253, 256, 257, 300, 509, 512, 513, 577, 768,
+                               1021, 1024, 1025, 1600, 2045, 2048, 2049, 3333, 4096, 4097, 6000, 8189, 8192])
+def test_low_and_poly(B, ctx, n, off):
+    import oracle as O
+    batch = 23 if n <= 512 else 5 if n <= 2048 else 2
+    a, b = operands(n, batch, n)
+    for prog, want in ((PROG_MUL_LOW, O.mul_low), (PROG_POLY, O.poly)):
+        out = G.empty_dev((batch * n + off,), np.uint32)[off:].reshape(batch, n)
+        B.fused(ctx, prog, padded(a, off), padded(b, off), out)
+        G.sync()
+        assert differing(G.from_dev(out, np.uint32), want(a, b)) == [], prog
