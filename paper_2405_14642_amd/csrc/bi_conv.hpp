@@ -152,6 +152,40 @@ __device__ __forceinline__ void small_steps(const uint8_t *ap, uint32_t sh, cons
     }
 }
 
+// The steps of tiles T0 .. T0 + T - 1 of a product with groups 0 .. GD of b
+// and steps up to U of a, straight-line: only MFMAs inside the band, the
+// operands of each step requested before the MFMAs of the one before it.
+template <int T0, int T, int GD, int U>
+__device__ __forceinline__ void static_steps(const uint8_t *ap, uint32_t sh, const uint8_t *bp, v4i (&acc)[T]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int J = (GD + 4 * k) / 16, j0 = k == 0 ? -1 : 0, M = (U - k) / 4;
+        const int mlo = T0 > J ? T0 - J : 0, mhi = M < T0 + T - 1 - j0 ? M : T0 + T - 1 - j0;
+        v4i w[(GD + 12) / 16 + 2];  // B operand j at j + 1
+#pragma unroll
+        for (int j = j0; j <= J; ++j)
+            if (j >= T0 - mlo && j <= T0 - mlo + T - 1) w[j + 1] = read_b(bp + 256 * j - 64 * k);
+        v4i a = align_a(read_a(ap + 64 * k + 256 * mlo), sh);
+#pragma unroll
+        for (int m = mlo; m <= mhi; ++m) {
+            ARaw next;
+            if (m < mhi) {
+                next = read_a(ap + 64 * k + 256 * (m + 1));
+                const int j = T0 - m - 1;
+                if (j >= j0 && j <= J) w[j + 1] = read_b(bp + 256 * j - 64 * k);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = T - 1; i >= 0; --i) {
+                const int j = T0 + i - m;
+                if (j >= j0 && j <= J) acc[i] = mac64(a, w[j + 1], acc[i]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (m < mhi) a = align_a(next, sh);
+        }
+    }
+}
+
 // LDS written by this wave is read by its other lanes: the LDS serves one
 // wave's instructions in order, so only the compiler has to keep them.
 __device__ __forceinline__ void wave_lds_fence() {

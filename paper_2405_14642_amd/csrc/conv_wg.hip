@@ -2,29 +2,34 @@
 // product: full products above 128 words, low products (mod 2^N) and Poly
 // above 256.  See bi_conv.hpp for the digits, tiles and operand layout.
 //
-// A unit is eight tiles (two rows of 256 words).  A wave owns UPW units and
-// walks, per residue kappa, the steps m of a unit with the eight B operands
-// j = t - m of its tiles in registers: one A and one new B operand per step
-// of eight MFMAs.  Steps where every tile is in band run straight; at the
-// ends of a band straight-line triangles leave out the MFMAs whose operand
-// is zero.  Products of one unit run straight-line altogether.
+// A unit is T tiles (T / 4 rows of 256 words), T a multiple of 4.  A wave
+// owns UPW units and walks, per residue kappa, the steps m of a unit with the
+// T B operands j = t - m of its tiles in registers: one A and one new B
+// operand per step of T MFMAs.  Two forms:
+//   straight-line (ST): all steps of the largest product unrolled, only the
+//     MFMAs inside the band; smaller products are padded with zero digits.
+//   loops, for any size: blocks of T steps, straight where every tile is in
+//     band and triangles at the ends of the band.
 //
-// What bounds it: the matrix cores from 1024 words up (at 1024 words a
-// product is 1120 MFMAs of 16 clk, 1024 of them inside the band: 17.9k clk
-// of one SIMD), the chain recode - steps - carries below, which four waves
-// per SIMD of several workgroups overlap.  Eight tiles per unit: the LDS
-// traffic per MFMA falls with the tiles (2.25 KB per step), the registers
-// grow (four accumulators and four B words per tile and lane); eight leave
-// 128 registers for four waves per SIMD.  Measured against the kernel before
-// it (32 x 32 x 32 tiles over 8-byte windows of a in LDS; three kernels and
-// global scratch above 1024 words): 4096 x 1024 words 81.4 -> 62.1 us (2.2e15
-// int8 ops/s), 8192 x 512 words 61.7 -> 40.7, 16384 x 256 words 51.9 -> 24.5,
-// 2048 x 2048 words 198 -> 102, 512 x 4096 words 196 -> 91 us.  Low products
-// and Poly against the VALU schoolbook in LDS: 16384 x 512 words 266 -> 40.5
-// us, 4096 x 2048 words (Poly) 3041 -> 408, 128 x 8192 words 657 -> 78 and
-// (Poly) 2631 -> 303.
+// What bounds it.  Random digits hold the chip at about 1.8 GHz (2.05e15
+// MAC/s for this MFMA from registers alone, 1.74e15 for 32 x 32 x 32), and the
+// LDS reads and vector work beside the MFMAs cost time on top of them: at
+// 8192 x 1024 words the MFMAs alone are 73 us of 104, and the loops took 68
+// without them.  Hence few operand reads per MFMA (T as large as the registers
+// allow where a product fits few units: 2.25 KB per T MFMAs), no MFMA outside
+// the band, and small workgroups: a wave that shares nothing waits for
+// nothing.  Above 1024 words T = 8 and 128 registers for four waves per SIMD
+// (T = 16 at two or three: 2048 words 99 -> 97-103 us, 1500 words 119 ->
+// 127-152).  Measured against the kernels before it (32 x 32 x 32 tiles over
+// 8-byte windows of a in LDS; three kernels and global scratch above 1024
+// words), full products: 16384 x 256 words 51.9 -> 24.5 us, 8192 x 512 words
+// 61.7 -> 28, 4096 x 1024 words 81.4 -> 54, 2048 x 2048 words 198 -> 95, 512 x
+// 4096 words 196 -> 87 us.  Low products and Poly against the VALU schoolbook
+// in LDS: 16384 x 512 words 266 -> 40 us, 4096 x 2048 words (Poly) 3041 ->
+// 390, 128 x 8192 words 657 -> 70 and (Poly) 2631 -> 277.
 #include <algorithm>
 #include <atomic>
+#include <utility>
 
 #include "bi_conv.hpp"
 
@@ -34,7 +39,6 @@ namespace {
 
 using namespace conv;
 
-constexpr int kT = 8;            // tiles per unit
 constexpr uint32_t kATail = 7;   // 16-byte pieces after a's digits (steps read up to 83 bytes past them)
 constexpr uint32_t kBPad = 32;   // zero groups below group 0 of b: B operand -2 at kappa 0, -1 above
 constexpr uint32_t kBTail = 35;  // groups from the top digit's on: B operand J + 1
@@ -58,63 +62,76 @@ template <int NW, bool LOW>
 __device__ __forceinline__ uint32_t wave_role(uint32_t wave, uint64_t inst) {
     if constexpr (NW == 1) return 0;
     else if constexpr (NW <= 4) return (wave + uint32_t(inst)) % NW;
-    else if constexpr (LOW) return (wave & 4u) ? (wave ^ 3u) : wave;
+    else if constexpr (LOW && NW % 8 == 0) return (wave & 4u) ? (wave ^ 3u) : wave;
     else return wave;
 }
 
-// Eight steps m .. m + 7 of a unit from a window w (slot i: B operand
+// T steps m .. m + T - 1 of a unit from a window w (slot i: B operand
 // t0 - m + i), sliding it as they go.  SHAPE: every tile in band (kAll); only
 // tiles i <= s of step s (kEntry: the first step takes the last B operand);
 // only tiles i >= s (kExit: the last step takes B operand 0).
 enum Shape { kAll, kEntry, kExit };
-template <int SHAPE>
-__device__ __forceinline__ void block8(const uint8_t *am, uint32_t sh, const uint8_t *bj, v4i (&w)[kT],
-                                       v4i (&acc)[kT]) {
-    ARaw next = read_a(am);
+// `a` holds the A operand of the first step, and on return that of step m + T
+// (`more`: there is one).  The scheduler is held to this order: operands of
+// the next step are requested before the MFMAs of this one and awaited after
+// them.
+template <int T, int SHAPE>
+__device__ __forceinline__ void block_steps(const uint8_t *am, uint32_t sh, const uint8_t *bj, v4i (&w)[T], v4i &a,
+                                       bool more, v4i (&acc)[T]) {
 #pragma unroll
-    for (int s = 0; s < kT; ++s) {
-        const v4i a = align_a(next, sh);
-        if (s + 1 < kT) next = read_a(am + 256 * (s + 1));
-#pragma unroll
-        for (int i = kT - 1; i >= 0; --i)
-            if (SHAPE == kAll || (SHAPE == kEntry ? i <= s : i >= s))
-                acc[i] = mac64(a, w[(i - s) & (kT - 1)], acc[i]);
+    for (int s = 0; s < T; ++s) {
+        const ARaw next = read_a(s + 1 < T || more ? am + 256 * (s + 1) : am);
+        __builtin_amdgcn_sched_barrier(0);
+        if (SHAPE != kEntry || s == T - 1) acc[T - 1] = mac64(a, w[(T - 1 - s) & (T - 1)], acc[T - 1]);
         // the window of the next step starts one B operand lower
-        if (SHAPE != kExit) w[(kT - 1 - s) & (kT - 1)] = read_b(bj - 256 * (s + 1));
+        if (SHAPE != kExit) w[(T - 1 - s) & (T - 1)] = read_b(bj - 256 * (s + 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = T - 2; i >= 1; --i)
+            if (SHAPE == kAll || (SHAPE == kEntry ? i <= s : i >= s))
+                acc[i] = mac64(a, w[(i - s) & (T - 1)], acc[i]);
+        __builtin_amdgcn_sched_barrier(0);
+        const v4i an = align_a(next, sh);
+        __builtin_amdgcn_sched_barrier(0);
+        if (SHAPE != kExit || s == 0) acc[0] = mac64(a, w[(0 - s) & (T - 1)], acc[0]);
+        a = an;
     }
 }
 
 // Adds the steps of the unit at tile t0 into acc.  U: last step with a
 // nonzero A operand; gd: last nonzero group of b.  B operands above J are
 // zero, and those below 0 but for -1 at kappa 0.
+template <int T>
 __device__ __forceinline__ void unit_steps(const uint8_t *ap, uint32_t sh, const uint8_t *bp, int32_t t0, int32_t U,
-                                           int32_t gd, v4i (&acc)[kT]) {
+                                           int32_t gd, v4i (&acc)[T]) {
 #pragma unroll 1
     for (int32_t k = 0; k < 4; ++k) {
         const int32_t J = (gd + 4 * k) >> 4, M = (U - k) >> 2;
         const uint8_t *ak = ap + 64 * k, *bk = bp - 64 * k;
         // the unit's band ends inside the steps of a (exit shape), or a ends first
-        const bool exits = M >= t0 + kT - 1;
+        const bool exits = M >= t0 + T - 1;
         int32_t m = max(0, t0 - J);
-        const int32_t end = exits ? t0 : min(M, t0 + kT) + 1;
-        if (exits || end - m >= kT) {
-            v4i w[kT];
+        const int32_t end = exits ? t0 : min(M, t0 + T) + 1;
+        if (exits || end - m >= T) {
+            v4i w[T];
 #pragma unroll
-            for (int i = 0; i < kT; ++i) w[i] = read_b(bk + 256 * min(t0 - m + i, J + 1));
+            for (int i = 0; i < T; ++i) w[i] = read_b(bk + 256 * min(t0 - m + i, J + 1));
+            v4i a = align_a(read_a(ak + 256 * m), sh);
             if (!exits && t0 >= J) {
-                block8<kEntry>(ak + 256 * m, sh, bk + 256 * (t0 - m), w, acc);
-                m += kT;
+                block_steps<T, kEntry>(ak + 256 * m, sh, bk + 256 * (t0 - m), w, a, m + T <= M, acc);
+                m += T;
             }
 #pragma unroll 1
-            for (; m + kT <= end; m += kT) block8<kAll>(ak + 256 * m, sh, bk + 256 * (t0 - m), w, acc);
+            for (; m + T <= end; m += T)
+                block_steps<T, kAll>(ak + 256 * m, sh, bk + 256 * (t0 - m), w, a, m + T <= M, acc);
             if (exits) {
-                block8<kExit>(ak + 256 * m, sh, bk + 256 * (t0 - m), w, acc);
-                m += kT;
+                block_steps<T, kExit>(ak + 256 * m, sh, bk + 256 * (t0 - m), w, a, false, acc);
+                m += T;
                 if (k == 0) {  // B operand -1 reaches 16 digits of the product below tile m
                     const v4i b = read_b(bk - 256);
 #pragma unroll
-                    for (int i = 0; i < kT; ++i)
-                        if (i < kT - 1 || m <= M)
+                    for (int i = 0; i < T; ++i)
+                        if (i < T - 1 || m <= M)
                             acc[i] = mac64(align_a(read_a(ak + 256 * (t0 + i + 1)), sh), b, acc[i]);
                 }
             }
@@ -122,17 +139,24 @@ __device__ __forceinline__ void unit_steps(const uint8_t *ap, uint32_t sh, const
 if (m < end) {  // fewer than eight steps left
             const int32_t least = k == 0 ? -2 : -1, cnt = end - m;
             const uint8_t *am = ak + 256 * m;
-            v4i w[kT];
+            v4i w[T];
 #pragma unroll
-            for (int i = 0; i < kT; ++i) w[i] = read_b(bk + 256 * max(min(t0 - m + i, J + 1), least));
-            ARaw next = read_a(am);
+            for (int i = 0; i < T; ++i) w[i] = read_b(bk + 256 * max(min(t0 - m + i, J + 1), least));
+            v4i a = align_a(read_a(am), sh);
 #pragma unroll
-            for (int s = 0; s < kT - 1; ++s) {
-                const v4i a = align_a(next, sh);
-                next = read_a(am + 256 * min(s + 1, cnt - 1));
+            for (int s = 0; s < T - 1; ++s) {
+                const ARaw next = read_a(am + 256 * min(s + 1, cnt - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                acc[T - 1] = mac64(a, w[(T - 1 - s) & (T - 1)], acc[T - 1]);
+                w[(T - 1 - s) & (T - 1)] = read_b(bk + 256 * max(t0 - m - s - 1, least));
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = kT - 1; i >= 0; --i) acc[i] = mac64(a, w[(i - s) & (kT - 1)], acc[i]);
-                w[(kT - 1 - s) & (kT - 1)] = read_b(bk + 256 * max(t0 - m - s - 1, least));
+                for (int i = T - 2; i >= 1; --i) acc[i] = mac64(a, w[(i - s) & (T - 1)], acc[i]);
+                __builtin_amdgcn_sched_barrier(0);
+                const v4i an = align_a(next, sh);
+                __builtin_amdgcn_sched_barrier(0);
+                acc[0] = mac64(a, w[(0 - s) & (T - 1)], acc[0]);
+                a = an;
                 if (s + 1 >= cnt) break;
             }
         }
@@ -140,15 +164,19 @@ if (m < end) {  // fewer than eight steps left
 }
 
 // One workgroup's view of a product.
-template <int NW, int UPW, int MODE>
+template <int NW, int UPW, int MODE, int T, bool ST>
 struct Wg {
     static constexpr bool LOW = MODE != kFull;
     static constexpr int NU = NW * UPW;          // units
-    static constexpr int RW = LOW ? 2 * UPW : UPW;  // operand rows per wave
-    static constexpr uint32_t CAP = 64 * RW * NW;   // operand chunks held by the workgroup
-    // one unit holds the whole product: straight-line steps for the largest
-    // size, smaller ones padded with zero digits
-    static constexpr bool ONE = NU == 1;
+    static constexpr int RU = T / 4;              // result rows per unit
+    static constexpr int NR = RU * UPW;           // result rows per wave
+    static constexpr int RW = LOW ? NR : (NR + 1) / 2;  // operand rows per wave
+    static constexpr uint32_t LANES = 64 * RW * NW;  // operand chunks the lanes can hold
+    static constexpr uint32_t CAP = (LOW ? 16 : 8) * T * NU;  // operand chunks of the largest product
+    // ST: straight-line steps for the largest size, smaller ones padded with
+    // zero digits
+    static constexpr int GD = int(CAP) - (LOW ? 1 : 0), UMAX = (16 * int(CAP) + (LOW ? 62 : 63)) / 64;
+    static_assert(!ST || UPW == 1, "straight-line steps take one unit per wave");
     static_assert(!LOW || UPW == 1, "low products take one unit per wave");
 
     uint8_t *lds;
@@ -218,60 +246,71 @@ struct Wg {
         }
     }
 
+    __device__ __forceinline__ bool stored(int i) const {
+        if constexpr (ST) return LANES <= CAP || chunk(i) <= CAP;
+        else return chunk(i) <= nch;
+    }
     // Digits into the area of a or b (the chunk of the top digit included).
     __device__ __forceinline__ void put_a(const uint32_t (&d)[RW][4]) const {
 #pragma unroll
         for (int i = 0; i < RW; ++i)
-            if (ONE || chunk(i) <= nch)
+            if (stored(i))
                 *reinterpret_cast<uint4 *>(lds + kAPad + 16 * chunk(i)) = make_uint4(d[i][0], d[i][1], d[i][2], d[i][3]);
     }
     __device__ __forceinline__ void put_b(const uint32_t (&d)[RW][4]) const {
 #pragma unroll
         for (int i = 0; i < RW; ++i)
-            if (ONE || chunk(i) <= nch) *reinterpret_cast<uint4 *>(lds + lo.b + 16 * (kBPad + chunk(i))) = reversed(d[i]);
+            if (stored(i)) *reinterpret_cast<uint4 *>(lds + lo.b + 16 * (kBPad + chunk(i))) = reversed(d[i]);
     }
     // The top digits where no lane holds their chunk.
     __device__ __forceinline__ void put_top(const uint32_t (&t)[2]) const {
-        if (nch == CAP && threadIdx.x == 0) {
+        if (nch == LANES && threadIdx.x == 0) {
             *reinterpret_cast<uint4 *>(lds + kAPad + 16 * nch) = make_uint4(t[0], 0, 0, 0);
             *reinterpret_cast<uint4 *>(lds + lo.b + 16 * (kBPad + nch)) = make_uint4(0, 0, 0, t[1] << 24);
         }
+    }
+
+    // The straight-line steps of this wave's unit.
+    template <int... Q>
+    __device__ __forceinline__ void unit_static(std::integer_sequence<int, Q...>, v4i (&acc)[T]) const {
+        const uint8_t *ap = lds + la.a, *bp = lds + lo.b + 16 * kBPad + la.b;
+        ((pw == uint32_t(Q) ? static_steps<Q * T, T, GD, UMAX>(ap, la.sh, bp, acc) : void()), ...);
     }
 
     // The product of the digits in LDS plus the words `add`: on return
     // s[2 u + i] holds chunk `lane` of row 2 unit(u) + i.  Two barriers; the
     // digit areas are free after the first.
     template <bool ADD>
-    __device__ __forceinline__ void product(const uint32_t (&add)[RW][4], uint32_t (&s)[2 * UPW][4]) const {
-        uint32_t x[2 * UPW][4], hv[2 * UPW][4];
+    __device__ __forceinline__ void product(const uint32_t (&add)[RW][4], uint32_t (&s)[NR][4]) const {
+        uint32_t x[NR][4], hv[NR][4];
         const int32_t gd = LOW ? int32_t(nch) - 1 : int32_t(nch);
         const int32_t U = (16 * int32_t(nch) + (LOW ? 62 : 63)) >> 6;
         const int32_t tiles = LOW ? int32_t(nch + 15) >> 4 : int32_t(nch + 7) >> 3;
         uint32_t *bnd = sums() + 64, *cs = sums() + 128;
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
-            v4i acc[kT] = {};
-            const int32_t t0 = kT * int32_t(unit(u));
-            if constexpr (ONE) small_steps<kT, LOW>(lds + la.a, la.sh, lds + lo.b + 16 * kBPad + la.b, acc);
-            else if (t0 < tiles) unit_steps(lds + la.a, la.sh, lds + lo.b + 16 * kBPad + la.b, t0, U, gd, acc);
-            row_words(acc[0], acc[1], acc[2], acc[3], x[2 * u], hv[2 * u]);
-            row_words(acc[4], acc[5], acc[6], acc[7], x[2 * u + 1], hv[2 * u + 1]);
-            if constexpr (ADD) {
-                add_to_words(x[2 * u], hv[2 * u], add[2 * u]);
-                add_to_words(x[2 * u + 1], hv[2 * u + 1], add[2 * u + 1]);
+            v4i acc[T] = {};
+            const int32_t t0 = T * int32_t(unit(u));
+            if constexpr (ST) unit_static(std::make_integer_sequence<int, NU>{}, acc);
+            else if (t0 < tiles) unit_steps<T>(lds + la.a, la.sh, lds + lo.b + 16 * kBPad + la.b, t0, U, gd, acc);
+#pragma unroll
+            for (int i = 0; i < RU; ++i) {
+                const int r = RU * u + i;
+                row_words(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3], x[r], hv[r]);
+                if constexpr (ADD) add_to_words(x[r], hv[r], add[r]);
             }
-            if (lane == 63) bnd[unit(u)] = hv[2 * u + 1][3];
+            if (lane == 63) bnd[unit(u)] = hv[RU * u + RU - 1][3];
         }
         __syncthreads();
-        uint64_t G[2 * UPW], P[2 * UPW];
+        uint64_t G[NR], P[NR];
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             const uint32_t un = unit(u);
             uint32_t out = 0, all = 1;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = 2 * u + i;
-                const uint32_t first = i ? uint32_t(__builtin_amdgcn_readlane(hv[2 * u][3], 63))
+            for (int i = 0; i < RU; ++i) {
+                const int r = RU * u + i;
+                const uint32_t first = i ? uint32_t(__builtin_amdgcn_readlane(hv[r - 1][3], 63))
                                          : un ? bnd[un - 1] : kBelowFirst;
                 const uint32_t y[4] = {from_below(hv[r][3], first), hv[r][0], hv[r][1], hv[r][2]};
                 const uint32_t g = add_words<4>(x[r], y, s[r]);
@@ -287,8 +326,8 @@ struct Wg {
         for (int u = 0; u < UPW; ++u) {
             uint32_t cin = NU > 1 ? carry_into(cs, NU, unit(u), nullptr) : 0u;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = 2 * u + i;
+            for (int i = 0; i < RU; ++i) {
+                const int r = RU * u + i;
                 const WaveCarry wc = wave_carry(G[r], P[r], cin);
                 add_carry_words<4>(s[r], uint32_t(wc.into >> lane) & 1u);
                 cin = wc.out;
@@ -307,10 +346,10 @@ struct Wg {
 
 }  // namespace
 
-template <int NW, int UPW, int MODE, class Src>
-__global__ __launch_bounds__(64 * NW, MODE == kPoly && NW < 16 ? 3 : 4) void conv_wg_kernel(Src src) {
+template <int NW, int UPW, int MODE, int T, bool ST, class Src>
+__global__ __launch_bounds__(64 * NW, T >= 16 || (T > 8 && MODE == kPoly) ? 2 : T > 8 || (MODE == kPoly && NW < 4) ? 3 : 4) void conv_wg_kernel(Src src) {
     extern __shared__ __align__(16) uint8_t lds[];
-    using W = Wg<NW, UPW, MODE>;
+    using W = Wg<NW, UPW, MODE, T, ST>;
     constexpr bool LOW = W::LOW;
     constexpr int RW = W::RW;
     const uint32_t wave = wave_in_block();
@@ -333,7 +372,7 @@ __global__ __launch_bounds__(64 * NW, MODE == kPoly && NW < 16 ? 3 : 4) void con
         w.pw = wave_role<NW, LOW>(wave, inst);
         w.n = in.n;
         w.nch = (in.n + 3) / 4;
-        w.lo = wg_layout(W::ONE ? W::CAP : w.nch);
+        w.lo = wg_layout(ST ? W::CAP : w.nch);
         uint32_t t[2];
         uint32_t b[RW][4];  // Poly: the words of b
         if constexpr (MODE == kPoly) {
@@ -343,7 +382,7 @@ __global__ __launch_bounds__(64 * NW, MODE == kPoly && NW < 16 ? 3 : 4) void con
                 for (int q = 0; q < 4; ++q) b[i][q] = y[i][q];
         }
         w.recode(x, y, t);
-        const uint32_t held = W::ONE ? W::CAP : w.nch;  // chunks of each digit area
+        const uint32_t held = ST ? W::CAP : w.nch;  // chunks of each digit area
         if (held != zeros_for) {  // uniform: the zero bytes around both digit areas
             zeros_for = held;
             const uint32_t za = kAPad / 16, zt = kATail, zb = kBPad, zu = kBTail;
@@ -361,7 +400,7 @@ __global__ __launch_bounds__(64 * NW, MODE == kPoly && NW < 16 ? 3 : 4) void con
         w.put_b(y);
         if constexpr (!LOW) w.put_top(t);
         __syncthreads();
-        uint32_t s[2 * UPW][4];
+        uint32_t s[W::NR][4];
         const uint64_t nxt = inst + gridDim.x;
         uint32_t da[RW][4], db[RW][4];
         if constexpr (MODE == kPoly) {
@@ -380,23 +419,23 @@ __global__ __launch_bounds__(64 * NW, MODE == kPoly && NW < 16 ? 3 : 4) void con
             }
         };
         if constexpr (MODE == kPoly) {
-            uint32_t ab[RW][4], T[RW][4], V[RW][4];
+            uint32_t ab[RW][4], u[RW][4], v[RW][4];
             w.template product<false>(b, ab);  // a b
             w.put_b(da);
             __syncthreads();
-            w.template product<true>(b, T);  // a a + b
+            w.template product<true>(b, u);  // a a + b
             w.put_a(db);
             w.put_b(db);
             __syncthreads();
-            w.template product<true>(b, V);  // b b + b
+            w.template product<true>(b, v);  // b b + b
 #pragma unroll
             for (int i = 0; i < RW; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (4 * w.chunk(i) + q >= w.n) { T[i][q] = 0; V[i][q] = 0; }
-            w.recode(T, V, t);
-            w.put_a(T);
-            w.put_b(V);
+                    if (4 * w.chunk(i) + q >= w.n) { u[i][q] = 0; v[i][q] = 0; }
+            w.recode(u, v, t);
+            w.put_a(u);
+            w.put_b(v);
             __syncthreads();
             prefetch();
             w.template product<true>(ab, s);  // (a a + b)(b b + b) + a b
@@ -408,15 +447,16 @@ __global__ __launch_bounds__(64 * NW, MODE == kPoly && NW < 16 ? 3 : 4) void con
 #pragma unroll
         for (int u = 0; u < UPW; ++u)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) store_chunk4(outp, nout, 64 * (2 * w.unit(u) + uint32_t(i)) + w.lane, s[2 * u + i]);
+            for (int i = 0; i < W::RU; ++i)
+                store_chunk4(outp, nout, 64 * (W::RU * w.unit(u) + uint32_t(i)) + w.lane, s[W::RU * u + i]);
     }
 }
 
-template <int NW, int UPW, int MODE, class Src>
+template <int NW, int UPW, int MODE, int T, bool ST, class Src>
 static hipError_t launch_wg(const Src &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus) {
-    using W = Wg<NW, UPW, MODE>;
-    const uint32_t lds_bytes = wg_layout(W::ONE ? W::CAP : (nmax + 3) / 4).total;
-    const void *fn = reinterpret_cast<const void *>(&conv_wg_kernel<NW, UPW, MODE, Src>);
+    using W = Wg<NW, UPW, MODE, T, ST>;
+    const uint32_t lds_bytes = wg_layout(ST ? W::CAP : (nmax + 3) / 4).total;
+    const void *fn = reinterpret_cast<const void *>(&conv_wg_kernel<NW, UPW, MODE, T, ST, Src>);
     // (LDS bytes << 32 | resident workgroups per CU) of the last launch shape
     static std::atomic<uint64_t> occ{0}, lds_set{0};
     hipError_t e = lds_limit_once(fn, lds_set);
@@ -429,21 +469,31 @@ static hipError_t launch_wg(const Src &src, uint32_t nmax, uint64_t count, hipSt
         o = (uint64_t(lds_bytes) << 32) | uint32_t(nblk < 1 ? 1 : nblk);
         occ.store(o, std::memory_order_relaxed);
     }
-    const uint64_t cap = uint64_t(uint32_t(o)) * uint64_t(num_cus > 0 ? num_cus : 1);
+    const uint64_t cap = uint64_t(uint32_t(o)) * uint64_t(num_cus > 0 ? num_cus : 1) * 8;
     const uint32_t grid = uint32_t(std::min(count, cap));
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL((conv_wg_kernel<NW, UPW, MODE, Src>), dim3(grid), dim3(64 * NW), lds_bytes, st, src);
+    hipLaunchKernelGGL((conv_wg_kernel<NW, UPW, MODE, T, ST, Src>), dim3(grid), dim3(64 * NW), lds_bytes, st, src);
     return hipGetLastError();
 }
 
+// Full products by size: one straight-line wave while its T = 4 tiles per 128
+// words fit the registers (up to 640 words: 2^24 words of 300 / 512 / 600
+// words take 121 / 110 / 122 us, in loops over two or three units 186 / 142 /
+// 190), two of them up to 768 words and above 896 (111 / 104 us, loops 140 /
+// 111; between the two the padding to 1024 costs more than it saves: 800
+// words 160, loops 143), else loops over one unit of 256 words per wave.
 template <class Src>
 static hipError_t launch_full(const Src &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus) {
-    if (nmax <= 256) return launch_wg<1, 1, kFull>(src, nmax, count, st, num_cus);
-    if (nmax <= 512) return launch_wg<2, 1, kFull>(src, nmax, count, st, num_cus);
-    if (nmax <= 1024) return launch_wg<4, 1, kFull>(src, nmax, count, st, num_cus);
-    if (nmax <= 2048) return launch_wg<8, 1, kFull>(src, nmax, count, st, num_cus);
-    if (nmax <= 4096) return launch_wg<16, 1, kFull>(src, nmax, count, st, num_cus);
-    return launch_wg<16, 2, kFull>(src, nmax, count, st, num_cus);
+    if (nmax <= 256) return launch_wg<1, 1, kFull, 8, true>(src, nmax, count, st, num_cus);
+    if (nmax <= 384) return launch_wg<1, 1, kFull, 12, true>(src, nmax, count, st, num_cus);
+    if (nmax <= 512) return launch_wg<1, 1, kFull, 16, true>(src, nmax, count, st, num_cus);
+    if (nmax <= 640) return launch_wg<1, 1, kFull, 20, true>(src, nmax, count, st, num_cus);
+    if (nmax <= 768) return launch_wg<2, 1, kFull, 12, true>(src, nmax, count, st, num_cus);
+    if (nmax > 896 && nmax <= 1024) return launch_wg<2, 1, kFull, 16, true>(src, nmax, count, st, num_cus);
+    if (nmax <= 1024) return launch_wg<4, 1, kFull, 8, false>(src, nmax, count, st, num_cus);
+    if (nmax <= 2048) return launch_wg<8, 1, kFull, 8, false>(src, nmax, count, st, num_cus);
+    if (nmax <= 4096) return launch_wg<16, 1, kFull, 8, false>(src, nmax, count, st, num_cus);
+    return launch_wg<16, 2, kFull, 8, false>(src, nmax, count, st, num_cus);
 }
 
 hipError_t launch_bigmul_mfma(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n32, uint64_t batch,
@@ -468,14 +518,22 @@ hipError_t launch_conv_fused(bool poly, const uint32_t *a, const uint32_t *b, ui
     if (n > kMaxLimbs32) return hipErrorInvalidValue;
     const LowInst src{{a, b, c, n, batch}};
     if (n <= kConvSmallLowMax) return launch_conv_small_low(poly, src, st, num_cus);
-#define BI_WG(W)                                              \
-    poly ? launch_wg<W, 1, kPoly>(src, n, batch, st, num_cus) \
-         : launch_wg<W, 1, kLow>(src, n, batch, st, num_cus)
-    if (n <= 512) return BI_WG(1);
-    if (n <= 1024) return BI_WG(2);
-    if (n <= 2048) return BI_WG(4);
-    if (n <= 4096) return BI_WG(8);
-    return BI_WG(16);
+    // Up to 1024 words one straight-line wave (2^24 words of 600 / 768 / 1024
+    // words: 90 / 58 / 54 us, Poly 335 / 236 / 197; in loops over units of 512
+    // words 142 / 101 / 62 and 546 / 393 / 236), above it a wave per unit.
+#define BI_WG(W, ST)                                                 \
+    poly ? launch_wg<W, 1, kPoly, 8, ST>(src, n, batch, st, num_cus) \
+         : launch_wg<W, 1, kLow, 8, ST>(src, n, batch, st, num_cus)
+    if (n <= 512) return BI_WG(1, true);
+    if (poly && n <= 768) return launch_wg<1, 1, kPoly, 12, true>(src, n, batch, st, num_cus);
+    if (poly && n <= 1024) return launch_wg<1, 1, kPoly, 16, true>(src, n, batch, st, num_cus);
+    if (poly && n > 1024 && n <= 1536) return launch_wg<3, 1, kPoly, 8, false>(src, n, batch, st, num_cus);
+    if (!poly && n <= 768) return launch_wg<1, 1, kLow, 12, true>(src, n, batch, st, num_cus);
+    if (!poly && n <= 1024) return launch_wg<1, 1, kLow, 16, true>(src, n, batch, st, num_cus);
+    if (n <= 1024) return BI_WG(2, false);
+    if (n <= 2048) return BI_WG(4, false);
+    if (n <= 4096) return BI_WG(8, false);
+    return BI_WG(16, false);
 #undef BI_WG
 }
 
