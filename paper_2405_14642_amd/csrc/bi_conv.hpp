@@ -57,11 +57,21 @@ __device__ __forceinline__ void load_chunk4(const uint32_t *p, uint32_t n, uint3
     }
 }
 
-// Stores the words of chunk c that lie below n.
-__device__ __forceinline__ void store_chunk4(uint32_t *p, uint32_t n, uint32_t c, const uint32_t (&x)[4]) {
+// Stores the words of chunk c that lie below n (`stream`, uniform: past the
+// caches).
+__device__ __forceinline__ void store_chunk4(uint32_t *p, uint32_t n, uint32_t c, const uint32_t (&x)[4], bool stream) {
     const uint32_t base = 4 * c;
     if (base + 4 <= n) {
-        *reinterpret_cast<u32x4_a4 *>(p + base) = u32x4{x[0], x[1], x[2], x[3]};
+        const u32x4 v = {x[0], x[1], x[2], x[3]};
+        u32x4_a4 *q = reinterpret_cast<u32x4_a4 *>(p + base);
+        if (stream) {
+            // kept apart from the other store: merged, it would lose the hint
+            asm volatile("" ::: "memory");
+            __builtin_nontemporal_store(v, q);
+            asm volatile("" ::: "memory");
+        } else {
+            *q = v;
+        }
     } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t)

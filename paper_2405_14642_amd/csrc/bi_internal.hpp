@@ -125,16 +125,26 @@ struct UniformInst {
     uint32_t *c;
     uint32_t n;
     uint64_t batch;
+    bool stream = false;  // results stored past the caches
     __device__ __forceinline__ uint64_t count() const { return batch; }
+    __device__ __forceinline__ bool streams() const { return stream; }
     __device__ __forceinline__ InstRef get(uint64_t p) const {
         return InstRef{a + p * n, b + p * n, c + p * 2 * n, n};
     }
 };
 
+// Results of `bytes` in all are stored non-temporally from half the L2 caches'
+// 32 MiB on: they would only displace the operands there (262144 x 32 words
+// 37.7 -> 33.2 us, 65536 x 128 words 40.1 -> 36.0, low products 16384 x 512
+// words 38.8 -> 35.2; non-temporal loads as well: 35.0, 39.1, 37.9).  Smaller
+// results, Karatsuba's base products among them, are read again from the L2.
+inline bool streamed_results(uint64_t bytes) { return bytes > (uint64_t(16) << 20); }
+
 // Uniform batch whose results have the operands' n words (mod 2^N).
 struct LowInst {
     UniformInst u;
     __device__ __forceinline__ uint64_t count() const { return u.batch; }
+    __device__ __forceinline__ bool streams() const { return u.stream; }
     __device__ __forceinline__ InstRef get(uint64_t p) const {
         return InstRef{u.a + p * u.n, u.b + p * u.n, u.c + p * u.n, u.n};
     }
@@ -161,6 +171,7 @@ struct ListInst {
     const uint32_t *count_ptr;
     uint32_t words_per_limb;  // 1 (32-bit limbs) or 2 (64-bit limbs)
     __device__ __forceinline__ uint64_t count() const { return *count_ptr; }
+    __device__ __forceinline__ bool streams() const { return false; }
     __device__ __forceinline__ InstRef get(uint64_t p) const {
         const bi_desc d = desc[list[p]];
         const uint32_t w = words_per_limb;

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256, MODE == kPoly ? 4 : MODE == kLow ? 5 : 6) void
             const uint64_t oi = g * S::IPW + oslot;
             if (oi < count) {
                 const InstRef out = src.get(oi);
-                store_chunk4(out.c, 2 * out.n, co, s);
+                store_chunk4(out.c, 2 * out.n, co, s, src.streams());
             }
         }
     } else {
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256, MODE == kPoly ? 4 : MODE == kLow ? 5 : 6) void
             const uint64_t oi = g * S::IPW + oslot;
             if (oi < count) {
                 const InstRef out = src.get(oi);
-                store_chunk4(out.c, n, co, s);
+                store_chunk4(out.c, n, co, s, src.streams());
             }
         }
     }

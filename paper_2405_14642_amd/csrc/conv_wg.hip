@@ -448,7 +448,8 @@ __global__ __launch_bounds__(64 * NW, T >= 16 || (T > 8 && MODE == kPoly) ? 2 : 
         for (int u = 0; u < UPW; ++u)
 #pragma unroll
             for (int i = 0; i < W::RU; ++i)
-                store_chunk4(outp, nout, 64 * (W::RU * w.unit(u) + uint32_t(i)) + w.lane, s[W::RU * u + i]);
+                store_chunk4(outp, nout, 64 * (W::RU * w.unit(u) + uint32_t(i)) + w.lane, s[W::RU * u + i],
+                             src.streams());
     }
 }
 
@@ -500,7 +501,7 @@ hipError_t launch_bigmul_mfma(const uint32_t *a, const uint32_t *b, uint32_t *c,
                               hipStream_t st, int num_cus) {
     if (batch == 0) return hipSuccess;
     if (n32 > kMaxLimbs32) return hipErrorInvalidValue;
-    const UniformInst src{a, b, c, n32, batch};
+    const UniformInst src{a, b, c, n32, batch, streamed_results(8 * uint64_t(n32) * batch)};
     if (n32 <= kConvSmallMax) return launch_conv_small_full(src, st, num_cus);
     return launch_full(src, n32, batch, st, num_cus);
 }
@@ -516,7 +517,7 @@ hipError_t launch_conv_fused(bool poly, const uint32_t *a, const uint32_t *b, ui
                              hipStream_t st, int num_cus) {
     if (batch == 0) return hipSuccess;
     if (n > kMaxLimbs32) return hipErrorInvalidValue;
-    const LowInst src{{a, b, c, n, batch}};
+    const LowInst src{{a, b, c, n, batch, streamed_results(4 * uint64_t(n) * batch)}};
     if (n <= kConvSmallLowMax) return launch_conv_small_low(poly, src, st, num_cus);
     // Up to 1024 words one straight-line wave (2^24 words of 600 / 768 / 1024
     // words: 90 / 58 / 54 us, Poly 335 / 236 / 197; in loops over units of 512
