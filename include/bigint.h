@@ -311,7 +311,8 @@ bi_status bi_tune_load(bi_ctx *ctx, const char *path);
  * bi_tune_set_valu replaces entries 0 .. n_in-1: (0, 0) restores the size
  * rule; otherwise q must be 2 or 4, waves 1, 2, 4, 8 or 16, and the schedule's
  * LDS must fit one CU for the class's largest size (BI_EINVAL otherwise;
- * nothing is changed then). */
+ * nothing is changed then).  Uniform products of up to 32 words run packed
+ * several to a wavefront whatever the schedule. */
 bi_status bi_tune_get_valu(const bi_ctx *ctx, int *q_out, int *waves_out, uint32_t n_out);
 bi_status bi_tune_set_valu(bi_ctx *ctx, const int *q_in, const int *waves_in, uint32_t n_in);
 

@@ -287,7 +287,11 @@ hipError_t launch_conv_fused(bool poly, const uint32_t *a, const uint32_t *b, ui
 constexpr uint32_t kConvSmallLowMax = 256;
 hipError_t launch_conv_small_low(bool poly, const LowInst &src, hipStream_t st, int num_cus);
 
-// Fused programs (BI_PROG_*).
+// Fused programs (BI_PROG_*).  Longest instance (32-bit words) of their packed
+// kernels, which also form full products of short operands on the VALU.
+constexpr uint32_t kPackedMaxWords = 32;
+hipError_t launch_packed_full(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
+                              hipStream_t st, int num_cus);
 hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n32, uint64_t batch,
                         hipStream_t st, int num_cus);
 

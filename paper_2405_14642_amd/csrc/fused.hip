@@ -33,10 +33,7 @@
 
 namespace bi {
 
-// Longest instance (32-bit words) of the packed product / Poly kernels, and
-// output words per lane.
-constexpr uint32_t kPackedMaxWords = 32;
-constexpr int kPackedQ = 2;
+constexpr int kPackedQ = 2;  // output words per lane of the packed kernels
 
 namespace {
 
@@ -278,11 +275,20 @@ __host__ __device__ inline uint32_t packed_area(uint32_t n, uint32_t sq) { retur
 
 }  // namespace
 
-// Same-length product (PROG = BI_PROG_MUL_LOW) or Poly (BI_PROG_POLY) of
-// instances of at most 64 Q words, 64 / 2^seg_log per wavefront, one
-// wavefront per workgroup.  LDS: per instance 2 (product) or 4 (Poly)
+constexpr int kPackedFull = 0;  // the full product, 2 n words
+typedef u32x2 __attribute__((aligned(4))) u32x2_a4;  // 8 bytes at any word address
+
+// Full product (PROG = kPackedFull), same-length product (BI_PROG_MUL_LOW) or
+// Poly (BI_PROG_POLY) of instances whose result has at most 64 Q words,
+// 64 / 2^seg_log per wavefront, one wavefront per workgroup.  LDS: per instance 2 (product) or 4 (Poly)
 // operand areas.  Poly keeps a b in registers, forms a a + b and b b + b in
 // registers and stores them as the operands of the last product.
+// What bounds it: per group of products a chain of one load, one LDS round
+// trip and n / 4 window steps, overlapped by eight waves per SIMD.  Full
+// products of 4 / 16 words (2^22 words in all, 13 us of HBM traffic at copy
+// rate): 15.6 / 21.2 us, one workgroup per product 430 / 140, the int8
+// tiles 97 / 29.  Loading the next group ahead measured 5-25 % slower at odd
+// sizes (the extra registers buy nothing that eight waves do not hide).
 template <int PROG>
 __global__ __launch_bounds__(64) void fused_packed_kernel(const uint32_t *__restrict__ a,
                                                           const uint32_t *__restrict__ b, uint32_t *__restrict__ out,
@@ -292,7 +298,8 @@ __global__ __launch_bounds__(64) void fused_packed_kernel(const uint32_t *__rest
     constexpr uint32_t NA = PROG == BI_PROG_POLY ? 4 : 2;
     const uint32_t lane = lane_id(), S = 1u << seg_log, ipw = 64u >> seg_log;
     const uint32_t j = lane & (S - 1u), slot = lane >> seg_log;
-    const uint32_t nq = (n + Q - 1) / Q;  // chunks per instance
+    const uint32_t nr = PROG == kPackedFull ? 2 * n : n;  // words of a result
+    const uint32_t nq = (nr + Q - 1) / Q;                 // chunks per instance
     const uint32_t aw = packed_area(n, S * Q);
     for (uint32_t t = lane; t < ipw * NA * aw; t += 64) lds[t] = 0;
     __syncthreads();
@@ -324,16 +331,20 @@ __global__ __launch_bounds__(64) void fused_packed_kernel(const uint32_t *__rest
 #pragma unroll
             for (int q = 0; q < Q; ++q) Z[q] = R[q];
         }
-        store_q<Q>(out + inst * n, n, j, valid, Z);
+        if constexpr (PROG == kPackedFull) {  // 2 n words: whole chunks of Q = 2
+            if (valid) *reinterpret_cast<u32x2_a4 *>(out + inst * nr + Q * j) = u32x2{Z[0], Z[1]};
+        } else {
+            store_q<Q>(out + inst * nr, nr, j, valid, Z);
+        }
         __syncthreads();  // the areas are rewritten by the next group
     }
 }
 
 namespace {
 
-// log2 of the lanes an instance of n words takes.
-uint32_t packed_seg_log(uint32_t n) {
-    const uint32_t lanes = (n + kPackedQ - 1) / kPackedQ;
+// log2 of the lanes an instance with results of nr words takes.
+uint32_t packed_seg_log(uint32_t nr) {
+    const uint32_t lanes = (nr + kPackedQ - 1) / kPackedQ;
     uint32_t seg_log = 0;
     while ((1u << seg_log) < lanes) ++seg_log;
     return seg_log;
@@ -363,7 +374,25 @@ hipError_t launch_persistent(uint32_t threads, const uint32_t *a, const uint32_t
     return hipGetLastError();
 }
 
+template <int PROG>
+hipError_t launch_packed(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch, hipStream_t st,
+                         int num_cus) {
+    const uint32_t seg_log = packed_seg_log(PROG == kPackedFull ? 2 * n : n);
+    const size_t lds = packed_lds_bytes(PROG == BI_PROG_POLY, n, seg_log);
+    const uint64_t waves = (batch + (64u >> seg_log) - 1) / (64u >> seg_log);
+    const uint32_t grid = uint32_t(std::min<uint64_t>(waves, uint64_t(num_cus > 0 ? num_cus : 1) * 32));
+    hipLaunchKernelGGL((fused_packed_kernel<PROG>), dim3(grid), dim3(64), lds, st, a, b, c, n, batch, seg_log);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_packed_full(const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
+                              hipStream_t st, int num_cus) {
+    if (n == 0 || n > kPackedMaxWords) return hipErrorInvalidValue;
+    if (batch == 0) return hipSuccess;
+    return launch_packed<kPackedFull>(a, b, c, n, batch, st, num_cus);
+}
 
 hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n, uint64_t batch,
                         hipStream_t st, int num_cus) {
@@ -397,16 +426,8 @@ hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint3
     // 13.3 / 18.0 / 32.0 us against 47.5 / 27.0 / 26.0 on the matrix cores,
     // whose tiles hold 64 words; Poly 51 / 55 / 107 against 161 / 85 / 84).
     if (n > kPackedMaxWords) return launch_conv_fused(poly, a, b, c, n, batch, st, num_cus);
-    const uint32_t seg_log = packed_seg_log(n);
-    const size_t lds = packed_lds_bytes(poly, n, seg_log);
-    const uint64_t waves = (batch + (64u >> seg_log) - 1) / (64u >> seg_log);
-    const uint32_t grid = uint32_t(std::min<uint64_t>(waves, uint64_t(num_cus > 0 ? num_cus : 1) * 32));
-    if (poly)
-        hipLaunchKernelGGL((fused_packed_kernel<BI_PROG_POLY>), dim3(grid), dim3(64), lds, st, a, b, c, n, batch, seg_log);
-    else
-        hipLaunchKernelGGL((fused_packed_kernel<BI_PROG_MUL_LOW>), dim3(grid), dim3(64), lds, st, a, b, c, n, batch,
-                           seg_log);
-    return hipGetLastError();
+    return poly ? launch_packed<BI_PROG_POLY>(a, b, c, n, batch, st, num_cus)
+                : launch_packed<BI_PROG_MUL_LOW>(a, b, c, n, batch, st, num_cus);
 }
 
 }  // namespace bi

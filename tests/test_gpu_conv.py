@@ -126,3 +126,18 @@ def test_low_and_poly(B, ctx, n, off):
         B.fused(ctx, prog, padded(a, off), padded(b, off), out)
         G.sync()
         assert differing(G.from_dev(out, np.uint32), want(a, b)) == [], prog
+
+
+VALU = 1
+
+
+# an instance takes 1, 2, 4 .. 32 lanes of two result words each
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32])
+def test_packed_full(B, ctx, orc, n, off):
+    for batch in (1, 3, 64, 20011):
+        a, b = operands(n, batch, n)
+        out = G.empty_dev((batch * 2 * n + off,), np.uint32)[off:].reshape(batch, 2 * n)
+        B.bigmul(ctx, padded(a, off), padded(b, off), out, algo=VALU)
+        G.sync()
+        assert differing(G.from_dev(out, np.uint32), orc.mul(a, b)) == [], (n, off, batch)
