@@ -2,8 +2,8 @@
 // as a carry scan, carried across workgroups; the paper leaves such sizes to
 // its slower fall-back versions, Section 5.1).
 //
-// Four stream-ordered kernels (the fix-up is two); no workgroup ever waits
-// on another:
+// Above 8192 tiles four stream-ordered kernels (the fix-up is two); no
+// workgroup ever waits on another:
 //  1. tile pass: the integer is cut into tiles of NW waves x U rows x 64
 //     chunks of W words.  A tile is added with carry-in 0 through the same
 //     thread -> wave -> workgroup ballot-adder hierarchy as the cooperative
@@ -32,6 +32,15 @@
 // 2^24 / 2^28-bit pair: 14.0 / 13.7 / 28.0 -> 11.7 / 11.4 / 32.9 us with two
 // passes (all-ones plus one: 19.9 / 21.8 / 48.5 -> 12.0 / 11.4 / 35.4 us).
 //
+// Up to 8192 tiles (2^25 words) one kernel takes the place of the scan and the
+// two fix-up kernels, whose launches cost more than they do: a wave per tile
+// finds the tile's carry-in as above and adds it.  One pair of 3 2^20 / 2^22 /
+// 2^23 / 2^25 words: 16.5 / 17.3 / 25.8 / 73.6 -> 9.4 / 11.7 / 21.6 / 69.9 us per
+// call (all ones plus one 24.9 / 26.2 / 46.3 / 119.9 -> 19.3 / 20.9 / 41.6 /
+// 119.3).  Beyond, the search through long runs of propagating tiles, which
+// every wave repeats, outweighs it (2^29 words, all ones plus one: 1917 ->
+// 2798 us) and the launches no longer matter (2^27 words 271 -> 266 us).
+//
 // The chunk width W (16, 8 or 4 bytes) follows the pointers' alignment; the
 // integer's length need not be a multiple of it: the missing words of the
 // last chunk read as all ones in a and zero in b (and as all ones when the
@@ -52,6 +61,7 @@ constexpr int kRowsPerTile = kLargeNW * kLargeU;
 constexpr int kScanThreads = 1024;
 constexpr uint64_t kMaxTileGrid = uint64_t(1) << 22;  // workgroups of the tile pass
 constexpr uint64_t kTwoPassTiles = 512;                // up to this many tiles: two passes
+constexpr uint64_t kResolveTiles = 8192;               // up to this many: a wave per tile finds its carry-in
 
 // Summary bytes are padded to whole 16-byte words; padding is never read as
 // a tile.
@@ -276,8 +286,28 @@ __global__ __launch_bounds__(256) void large_add_fixup_kernel(uint32_t *out, con
     }
 }
 
-// One wavefront per listed tile: adds the carry from the tile's first chunk,
-// a row of 64 chunks per step, until a chunk that is not all ones.
+// Adds a carry into tile t's stored sum from its first chunk on, a row of 64
+// chunks per step, until a chunk that is not all ones.
+template <int W>
+__device__ __forceinline__ void walk_tile(uint32_t *out, uint64_t t, uint64_t m, uint32_t tail, uint32_t lane) {
+    for (uint32_t r = 0; r < uint32_t(kRowsPerTile); ++r) {
+        const uint64_t c = (t * kRowsPerTile + r) * 64 + lane;
+        const bool ok = c < m;
+        uint32_t s[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) s[w] = 0;
+        if (ok) load_chunk<W, false>(out, c, m, tail, 0xFFFFFFFFu, s);
+        const uint64_t stop = ballot(!ok || !all_ones<W>(s));
+        const uint32_t first = stop ? uint32_t(__builtin_ctzll(stop)) : 64u;
+        if (ok && lane <= first) {
+            add_carry_words<W>(s, 1u);
+            store_chunk<W, false>(out, c, m, tail, s);
+        }
+        if (stop) break;  // uniform
+    }
+}
+
+// One wavefront per listed tile.
 template <int W>
 __global__ __launch_bounds__(256) void large_add_walk_kernel(uint32_t *out, uint64_t m, uint32_t tail,
                                                              const uint32_t *walk_list, const uint32_t *walk_count) {
@@ -286,21 +316,63 @@ __global__ __launch_bounds__(256) void large_add_walk_kernel(uint32_t *out, uint
     const uint32_t count = __builtin_amdgcn_readfirstlane(*walk_count);
     for (uint64_t i = wave_global(); i < count; i += nwaves) {
         const uint64_t t = __builtin_amdgcn_readfirstlane(walk_list[i]);
-        for (uint32_t r = 0; r < uint32_t(kRowsPerTile); ++r) {
-            const uint64_t c = (t * kRowsPerTile + r) * 64 + lane;
-            const bool ok = c < m;
-            uint32_t s[W];
+        walk_tile<W>(out, t, m, tail, lane);
+    }
+}
+
+// Carry out of the tiles below tile t: that of the nearest one that does not
+// only propagate (below tile 0 nothing carries).  The wave reads the 64
+// nearest summaries, which nearly always hold it, then 1024 at a time (16 per
+// lane; the summary array starts at a 16-byte boundary).
+__device__ __forceinline__ uint32_t carry_from_below(const uint8_t *summary, uint64_t t, uint32_t lane) {
+    const int64_t near = int64_t(t) - 1 - int64_t(lane);
+    const uint32_t sv = near >= 0 ? summary[near] : 0u;
+    uint64_t stop = ballot((sv & 2u) == 0);
+    if (stop) return uint32_t(__builtin_amdgcn_readlane(int(sv), __builtin_ctzll(stop))) & 1u;
+    // tiles t - 64 .. t - 1 only propagate
+    for (int64_t top = (int64_t(t) - 64 + 15) / 16; top > 0; top -= 64) {
+        const int64_t w = top - 1 - int64_t(lane);  // 16 tiles per word, nearest word first
+        uint32_t found = 0, g = 0;
+        if (w >= 0) {
+            const uint4 v = reinterpret_cast<const uint4 *>(summary)[w];
+            const uint32_t in[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int w = 0; w < W; ++w) s[w] = 0;
-            if (ok) load_chunk<W, false>(out, c, m, tail, 0xFFFFFFFFu, s);
-            const uint64_t stop = ballot(!ok || !all_ones<W>(s));
-            const uint32_t first = stop ? uint32_t(__builtin_ctzll(stop)) : 64u;
-            if (ok && lane <= first) {
-                add_carry_words<W>(s, 1u);
-                store_chunk<W, false>(out, c, m, tail, s);
+            for (int j = 0; j < 16; ++j) {  // the highest tile below t that does not only propagate
+                const uint32_t x = (in[j >> 2] >> (8 * (j & 3))) & 3u;
+                if (uint64_t(16 * w + j) < t && (x & 2u) == 0) { found = 1; g = x & 1u; }
             }
-            if (stop) break;  // uniform
         }
+        stop = ballot(found != 0);
+        if (stop) return uint32_t(__builtin_amdgcn_readlane(int(g), __builtin_ctzll(stop)));
+    }
+    return 0u;
+}
+
+// One wavefront per tile: finds the tile's carry-in and, if it is 1, adds it
+// into the stored sum: usually into the first chunk alone, else a row of 64
+// chunks per step until a chunk that is not all ones.
+template <int W>
+__global__ __launch_bounds__(256) void large_add_resolve_kernel(uint32_t *out, const uint8_t *summary,
+                                                                uint8_t *carry_out, uint64_t m, uint32_t tail,
+                                                                uint64_t tiles) {
+    const uint32_t lane = lane_id();
+    const uint64_t nwaves = (uint64_t(gridDim.x) * blockDim.x) >> 6;
+    for (uint64_t t = wave_global(); t < tiles; t += nwaves) {
+        const uint32_t cin = carry_from_below(summary, t, lane);
+        if (carry_out && t == tiles - 1 && lane == 0) {
+            const uint32_t sv = summary[t];
+            *carry_out = uint8_t((sv & 1u) | ((sv >> 1) & cin));
+        }
+        if (!cin) continue;  // uniform
+        const uint64_t c0 = t * kRowsPerTile * 64;
+        uint32_t s[W];
+        load_chunk<W, false>(out, c0, m, tail, 0xFFFFFFFFu, s);
+        if (!all_ones<W>(s)) {  // uniform: every lane reads the first chunk
+            add_carry_words<W>(s, 1u);
+            if (lane == 0) store_chunk<W, false>(out, c0, m, tail, s);
+            continue;
+        }
+        walk_tile<W>(out, t, m, tail, lane);
     }
 }
 
@@ -330,6 +402,11 @@ hipError_t launch_large_w(const uint32_t *a, const uint32_t *b, uint32_t *out, u
     }
     hipLaunchKernelGGL((large_add_tile_kernel<W, NT>), dim3(uint32_t(grid)), dim3(64 * kLargeNW), 0, st, a, b, out,
                        summary, m, tail, tiles, nullptr);
+    if (tiles <= kResolveTiles) {
+        hipLaunchKernelGGL((large_add_resolve_kernel<W>), dim3(uint32_t((tiles + 3) / 4)), dim3(256), 0, st, out,
+                           summary, carry, m, tail, tiles);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(large_add_scan_kernel, dim3(1), dim3(kScanThreads), 0, st,
                        reinterpret_cast<const uint4 *>(summary), reinterpret_cast<uint4 *>(tile_cin), carry, walk_count,
                        tiles);

@@ -159,3 +159,34 @@ def test_many_tiles_scan_runs(B, ctx, orc):
     a, b = W.large_add_inputs(n, "chains")
     got, c = run(B, ctx, a, b, shift=1)
     check(orc, a, b, got, c)
+
+
+# a wave per tile finds its carry-in between 513 and 8192 tiles: 64 summaries,
+# then 1024 at a time, so runs of tiles that only propagate end at each of
+# those distances; shifted pointers make the chunks and with them the tiles
+# 2 or 4 times as many; 8193 tiles take the four kernels
+@pytest.mark.parametrize("n,shift", [(513 * 4096 - 7, 0), (2200 * 4096 + 5, 0), (513 * 2048 + 3, 2), (1500 * 1024 + 1, 1),
+                                     (8192 * 4096, 0), (8192 * 4096 + 1, 0)])
+def test_resolve_runs(B, ctx, orc, n, shift):
+    words = {0: 4096, 1: 1024, 2: 2048}[shift]
+    tiles = (n + words - 1) // words
+    rng = np.random.default_rng(n)
+    a = rng.integers(0, 2**32, n, dtype=np.uint32)
+    b = rng.integers(0, 2**32, n, dtype=np.uint32)
+    at = 1
+    for run_len in (1, 2, 62, 63, 64, 65, 80, 300, 1023, 1087, 1088, 1089, 1500):
+        if at + run_len + 2 >= tiles:
+            break
+        lo, hi = at * words, (at + run_len + 1) * words
+        a[lo:hi] = 0xFFFFFFFF  # the first tile generates, the others propagate
+        b[lo:hi] = 0
+        b[lo] = 1
+        at += run_len + 3
+    got, c = run(B, ctx, a, b, shift)
+    check(orc, a, b, got, c)
+    # the carry out of a run that ends with the integer
+    a[(tiles - min(tiles, 1200)) * words:] = 0xFFFFFFFF
+    b[(tiles - min(tiles, 1200)) * words:] = 0
+    b[(tiles - min(tiles, 1200)) * words] = 1
+    got, c = run(B, ctx, a, b, shift)
+    check(orc, a, b, got, c)
