@@ -56,6 +56,26 @@ __global__ void bin_kernel(const bi_desc *__restrict__ desc, uint64_t count, con
     }
 }
 
+// The same for few descriptors, by one workgroup that counts in LDS: no launch
+// to clear the counts.
+__global__ __launch_bounds__(1024) void bin_small_kernel(const bi_desc *__restrict__ desc, uint64_t count,
+                                                         const uint64_t *count_ptr, uint32_t words_per_limb,
+                                                         uint32_t *counts, uint32_t *lists, uint64_t stride) {
+    __shared__ uint32_t slots[kNumClasses];
+    if (count_ptr) count = min(*count_ptr, stride);
+    if (threadIdx.x < kNumClasses) slots[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint64_t i = threadIdx.x; i < count; i += 1024) {
+        const uint32_t n32 = desc[i].n_limbs * words_per_limb;
+        if (n32 == 0 || n32 > kMaxLimbs32) continue;
+        const uint32_t c = size_class(n32);
+        lists[uint64_t(c) * stride + atomicAdd(&slots[c], 1u)] = uint32_t(i);
+    }
+    __syncthreads();
+    if (threadIdx.x < kNumClasses) counts[threadIdx.x] = slots[threadIdx.x];
+}
+constexpr uint64_t kBinSmall = 4096;
+
 // counts (256 B), class lists, then the NTT transforms (256-byte aligned).
 static size_t lists_bytes(uint64_t count) {
     return (size_t(kNumClasses) * count * sizeof(uint32_t) + 255) & ~size_t(255);
@@ -95,14 +115,31 @@ hipError_t launch_bigmul_list_algo(const Ctx &c, const Tune &tune, const ListIns
     }
 }
 
-// The list kernel of size class k's algorithm (the tuned one, or `algo` when
-// it is forced and supports the class) over at most count_max instances.
-static hipError_t launch_class(const Ctx &c, const Tune &tune, const ListInst &src, uint32_t k, uint64_t count_max,
-                               int algo, void *scr, hipStream_t st) {
-    const uint32_t nmax = class_nmax(k);
-    int alg = tune.list_algo[k];
-    if (algo != BI_MUL_AUTO && algo_supports(algo, nmax)) alg = algo;
-    return launch_bigmul_list_algo(c, tune, src, nmax, count_max, alg, scr, class_scratch_bytes(count_max), st);
+// The list kernels of every size class's algorithm (the tuned one, or `algo`
+// when it is forced and supports the class): class k's list is cls(k), of at
+// most count(k) instances (0: nothing to launch).  The int8-MFMA classes of
+// up to 128 words share one launch: a stream burst of 1000 pairs fills no
+// class's grid, and each launch costs 4 to 5 us.
+template <class Cls, class Count>
+static hipError_t launch_classes(const Ctx &c, const Tune &tune, const Cls &cls, const Count &count, int algo, void *scr,
+                                 hipStream_t st) {
+    SmallLists small{};
+    uint64_t small_count[4] = {};
+    for (uint32_t k = 0; k < kNumClasses; ++k) {
+        const uint64_t n = count(k);
+        if (n == 0) continue;
+        const uint32_t nmax = class_nmax(k);
+        int alg = tune.list_algo[k];
+        if (algo != BI_MUL_AUTO && algo_supports(algo, nmax)) alg = algo;
+        if (k < 4 && alg == BI_MUL_SCHOOL_MFMA) {
+            small.cls[k] = cls(k);
+            small_count[k] = n;
+            continue;
+        }
+        const hipError_t e = launch_bigmul_list_algo(c, tune, cls(k), nmax, n, alg, scr, class_scratch_bytes(n), st);
+        if (e != hipSuccess) return e;
+    }
+    return launch_conv_small_lists(small, small_count, st, c.num_cus);
 }
 
 hipError_t launch_bigmul_v_binned(const Ctx &c, const Tune &tune, const void *a, const void *b, void *out,
@@ -113,16 +150,12 @@ hipError_t launch_bigmul_v_binned(const Ctx &c, const Tune &tune, const void *a,
     auto A = static_cast<const uint32_t *>(a);
     auto B = static_cast<const uint32_t *>(b);
     auto C = static_cast<uint32_t *>(out);
-    uint64_t off = 0;
-    for (uint32_t k = 0; k < kNumClasses; ++k) {
-        const uint64_t n = host_counts[k];
-        if (n == 0) continue;
-        const ListInst src{A, B, C, desc, lists + off, counts + k, wpl};
-        const hipError_t e = launch_class(c, tune, src, k, n, algo, scratch, st);
-        if (e != hipSuccess) return e;
-        off += n;
-    }
-    return hipSuccess;
+    auto cls = [&](uint32_t k) {
+        uint64_t off = 0;
+        for (uint32_t i = 0; i < k; ++i) off += host_counts[i];
+        return ListInst{A, B, C, desc, lists + off, counts + k, wpl};
+    };
+    return launch_classes(c, tune, cls, [&](uint32_t k) { return uint64_t(host_counts[k]); }, algo, scratch, st);
 }
 
 hipError_t launch_bigmul_v_core(const Ctx &c, const Tune &tune, const void *a, const void *b, void *out,
@@ -132,21 +165,22 @@ hipError_t launch_bigmul_v_core(const Ctx &c, const Tune &tune, const void *a, c
     uint32_t *lists = reinterpret_cast<uint32_t *>(static_cast<char *>(scratch) + 256);
     void *cls_scr = static_cast<char *>(scratch) + 256 + lists_bytes(count_max);
     const uint32_t wpl = limb_bits / 32;
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, counts, uint32_t(kNumClasses));
-    const uint64_t bins = (count_max + 255) / 256;
-    hipLaunchKernelGGL(bin_kernel, dim3(uint32_t(bins < 4096 ? bins : 4096)), dim3(256), 0, st, desc, count_max,
-                       count_ptr, wpl, counts, lists, count_max);
+    if (count_max <= kBinSmall) {
+        hipLaunchKernelGGL(bin_small_kernel, dim3(1), dim3(1024), 0, st, desc, count_max, count_ptr, wpl, counts, lists,
+                           count_max);
+    } else {
+        hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, counts, uint32_t(kNumClasses));
+        const uint64_t bins = (count_max + 255) / 256;
+        hipLaunchKernelGGL(bin_kernel, dim3(uint32_t(bins < 4096 ? bins : 4096)), dim3(256), 0, st, desc, count_max,
+                           count_ptr, wpl, counts, lists, count_max);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     auto A = static_cast<const uint32_t *>(a);
     auto B = static_cast<const uint32_t *>(b);
     auto C = static_cast<uint32_t *>(out);
-    for (uint32_t k = 0; k < kNumClasses; ++k) {
-        const ListInst src{A, B, C, desc, lists + uint64_t(k) * count_max, counts + k, wpl};
-        e = launch_class(c, tune, src, k, count_max, algo, cls_scr, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    auto cls = [&](uint32_t k) { return ListInst{A, B, C, desc, lists + uint64_t(k) * count_max, counts + k, wpl}; };
+    return launch_classes(c, tune, cls, [&](uint32_t) { return count_max; }, algo, cls_scr, st);
 }
 
 bi_status dispatch_bigmul_v(Ctx &c, const void *a, const void *b, void *out, const bi_desc *desc, uint64_t count,

@@ -59,6 +59,64 @@ __device__ __forceinline__ void small_finish(const v4i (&acc)[4], const uint32_t
     add_carry_words<4>(s, uint32_t(wc.into >> lane) & 1u);
 }
 
+// Full products of src on this wave: groups first, first + stride, ..; lds
+// holds Small<TPI, false>::WAVE bytes.
+template <int TPI, class Src>
+__device__ __forceinline__ void small_full(const Src &src, uint8_t *lds, uint64_t first, uint64_t stride) {
+    using S = Small<TPI, false>;
+    const uint32_t lane = lane_id();
+    const uint64_t count = src.count();
+    const uint64_t groups = (count + S::IPW - 1) / S::IPW;
+
+    // everything but the digits stays zero for the whole launch
+    for (uint32_t i = lane; i < S::WAVE / 16; i += 64) *reinterpret_cast<uint4 *>(lds + 16 * i) = make_uint4(0, 0, 0, 0);
+
+    const LaneAddr la = lane_addr();
+    const uint8_t *ap = lds + la.a, *bp = lds + S::AB + 16 * S::kPad + la.b;
+    const uint32_t co = lane & (16 * TPI - 1), oslot = lane / (16 * TPI);  // output chunk of this lane
+            // operand chunk of this lane
+            const uint32_t half = lane >> 5, l = lane & 31u;
+            const uint32_t slot = l / S::CPI, c = l & (S::CPI - 1);
+            const uint64_t keep = TPI == 4 ? ~0x8000000080000000ull : TPI == 2 ? ~0x8000800080008000ull : ~0x8080808080808080ull;
+            uint8_t *dst = lds + slot * S::INST + (half ? S::AB + 16 * (S::kPad + c) : kAPad + 16 * c);
+            uint32_t *tdst = reinterpret_cast<uint32_t *>(dst + 16 + (half ? 12 : 0));  // digit D of the operand
+            auto fetch = [&](uint64_t g, uint32_t (&x)[4], uint32_t &n) {
+                const uint64_t inst = g * S::IPW + slot;
+                n = 0;
+                if (inst < count) {
+                    const InstRef in = src.get(inst);
+                    n = in.n;
+                    load_chunk4(half ? in.b : in.a, in.n, c, x);
+                }
+            };
+            uint32_t xn[4] = {0, 0, 0, 0}, nn = 0;
+            uint64_t g = first;
+            if (g < groups) fetch(g, xn, nn);
+            for (; g < groups; g += stride) {
+                uint32_t x[4] = {xn[0], xn[1], xn[2], xn[3]};
+                const uint32_t n = nn;
+                if (g + stride < groups) fetch(g + stride, xn, nn);
+                const bool digits = 4 * c < n;
+                if (!digits) { x[0] = x[1] = x[2] = x[3] = 0; }
+                const uint32_t t = recode_lane(x, digits, keep, lane);
+                wave_lds_fence();
+                const uint4 rv = reversed(x);
+                *reinterpret_cast<uint4 *>(dst) = half ? rv : make_uint4(x[0], x[1], x[2], x[3]);
+                if (c == S::CPI - 1) *tdst = half ? t << 24 : t;
+                wave_lds_fence();
+                v4i acc[4] = {};
+    #pragma unroll
+                for (int i = 0; i < S::IPW; ++i) small_steps<TPI, false>(ap + i * S::INST, la.sh, bp + i * S::INST, acc + i * TPI);
+                uint32_t s[4];
+                small_finish<TPI, false>(acc, s, lane, s);
+                const uint64_t oi = g * S::IPW + oslot;
+                if (oi < count) {
+                    const InstRef out = src.get(oi);
+                    store_chunk4(out.c, 2 * out.n, co, s, src.streams());
+                }
+            }
+}
+
 }  // namespace
 
 template <int TPI, int MODE, class Src>
@@ -68,60 +126,18 @@ __global__ __launch_bounds__(256, MODE == kPoly ? 4 : MODE == kLow ? 5 : 6) void
     __shared__ __align__(16) uint8_t lds_all[4 * S::WAVE];
     const uint32_t lane = lane_id(), wave = wave_in_block();
     uint8_t *lds = lds_all + wave * S::WAVE;
-    const uint64_t count = src.count();
-    const uint64_t groups = (count + S::IPW - 1) / S::IPW;
-    const uint64_t stride = uint64_t(gridDim.x) * 4;
-
-    // everything but the digits stays zero for the whole launch
-    for (uint32_t i = lane; i < S::WAVE / 16; i += 64) *reinterpret_cast<uint4 *>(lds + 16 * i) = make_uint4(0, 0, 0, 0);
-
-    const LaneAddr la = lane_addr();
-    const uint8_t *ap = lds + la.a, *bp = lds + S::AB + 16 * S::kPad + la.b;
-    const uint32_t co = lane & (16 * TPI - 1), oslot = lane / (16 * TPI);  // output chunk of this lane
-
     if constexpr (!LOW) {
-        // operand chunk of this lane
-        const uint32_t half = lane >> 5, l = lane & 31u;
-        const uint32_t slot = l / S::CPI, c = l & (S::CPI - 1);
-        const uint64_t keep = TPI == 4 ? ~0x8000000080000000ull : TPI == 2 ? ~0x8000800080008000ull : ~0x8080808080808080ull;
-        uint8_t *dst = lds + slot * S::INST + (half ? S::AB + 16 * (S::kPad + c) : kAPad + 16 * c);
-        uint32_t *tdst = reinterpret_cast<uint32_t *>(dst + 16 + (half ? 12 : 0));  // digit D of the operand
-        auto fetch = [&](uint64_t g, uint32_t (&x)[4], uint32_t &n) {
-            const uint64_t inst = g * S::IPW + slot;
-            n = 0;
-            if (inst < count) {
-                const InstRef in = src.get(inst);
-                n = in.n;
-                load_chunk4(half ? in.b : in.a, in.n, c, x);
-            }
-        };
-        uint32_t xn[4] = {0, 0, 0, 0}, nn = 0;
-        uint64_t g = uint64_t(blockIdx.x) * 4 + wave;
-        if (g < groups) fetch(g, xn, nn);
-        for (; g < groups; g += stride) {
-            uint32_t x[4] = {xn[0], xn[1], xn[2], xn[3]};
-            const uint32_t n = nn;
-            if (g + stride < groups) fetch(g + stride, xn, nn);
-            const bool digits = 4 * c < n;
-            if (!digits) { x[0] = x[1] = x[2] = x[3] = 0; }
-            const uint32_t t = recode_lane(x, digits, keep, lane);
-            wave_lds_fence();
-            const uint4 rv = reversed(x);
-            *reinterpret_cast<uint4 *>(dst) = half ? rv : make_uint4(x[0], x[1], x[2], x[3]);
-            if (c == S::CPI - 1) *tdst = half ? t << 24 : t;
-            wave_lds_fence();
-            v4i acc[4] = {};
-#pragma unroll
-            for (int i = 0; i < S::IPW; ++i) small_steps<TPI, LOW>(ap + i * S::INST, la.sh, bp + i * S::INST, acc + i * TPI);
-            uint32_t s[4];
-            small_finish<TPI, false>(acc, s, lane, s);
-            const uint64_t oi = g * S::IPW + oslot;
-            if (oi < count) {
-                const InstRef out = src.get(oi);
-                store_chunk4(out.c, 2 * out.n, co, s, src.streams());
-            }
-        }
+        small_full<TPI>(src, lds, uint64_t(blockIdx.x) * 4 + wave, uint64_t(gridDim.x) * 4);
     } else {
+        const uint64_t count = src.count();
+        const uint64_t groups = (count + S::IPW - 1) / S::IPW;
+        const uint64_t stride = uint64_t(gridDim.x) * 4;
+        // everything but the digits stays zero for the whole launch
+        for (uint32_t i = lane; i < S::WAVE / 16; i += 64)
+            *reinterpret_cast<uint4 *>(lds + 16 * i) = make_uint4(0, 0, 0, 0);
+        const LaneAddr la = lane_addr();
+        const uint8_t *ap = lds + la.a, *bp = lds + S::AB + 16 * S::kPad + la.b;
+        const uint32_t co = lane & (16 * TPI - 1), oslot = lane / (16 * TPI);  // chunk of this lane
         // operand and result chunk of this lane coincide (a top carry digit
         // only reaches coefficients above the low half)
         const uint64_t keep = TPI == 4 ? ~(1ull << 63) : TPI == 2 ? ~0x8000000080000000ull : ~0x8000800080008000ull;
@@ -196,6 +212,32 @@ __global__ __launch_bounds__(256, MODE == kPoly ? 4 : MODE == kLow ? 5 : 6) void
             }
         }
     }
+}
+
+// The ragged classes of up to 16, 32, 64 and 128 words in one launch: blocks
+// first[k] .. first[k + 1] - 1 walk class k's list.
+__global__ __launch_bounds__(256, 5) void conv_small_lists_kernel(SmallLists p) {
+    __shared__ __align__(16) uint8_t lds_all[4 * Small<1, false>::WAVE];
+    static_assert(Small<1, false>::WAVE >= Small<2, false>::WAVE && Small<2, false>::WAVE >= Small<4, false>::WAVE,
+                  "one tile per instance takes the most LDS");
+    const uint32_t wave = wave_in_block(), blk = blockIdx.x;
+    uint8_t *lds = lds_all + wave * Small<1, false>::WAVE;
+    const uint32_t k = blk < p.first[1] ? 0 : blk < p.first[2] ? 1 : blk < p.first[3] ? 2 : 3;
+    const uint64_t first = uint64_t(blk - p.first[k]) * 4 + wave, stride = uint64_t(p.first[k + 1] - p.first[k]) * 4;
+    if (k < 2) small_full<1>(k == 0 ? p.cls[0] : p.cls[1], lds, first, stride);
+    else if (k == 2) small_full<2>(p.cls[2], lds, first, stride);
+    else small_full<4>(p.cls[3], lds, first, stride);
+}
+
+hipError_t launch_conv_small_lists(SmallLists p, const uint64_t (&count)[4], hipStream_t st, int num_cus) {
+    const uint64_t cap = uint64_t(num_cus > 0 ? num_cus : 1) * 4;  // blocks per class: they loop beyond it
+    const uint32_t ipw[4] = {4, 4, 2, 1};
+    p.first[0] = 0;
+    for (int k = 0; k < 4; ++k)
+        p.first[k + 1] = p.first[k] + uint32_t(std::min<uint64_t>((count[k] + 4 * ipw[k] - 1) / (4 * ipw[k]), cap));
+    if (p.first[4] == 0) return hipSuccess;
+    hipLaunchKernelGGL(conv_small_lists_kernel, dim3(p.first[4]), dim3(256), 0, st, p);
+    return hipGetLastError();
 }
 
 template <int TPI, int MODE, class Src>
