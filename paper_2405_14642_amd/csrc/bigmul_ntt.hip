@@ -126,8 +126,8 @@ __device__ __forceinline__ uint32_t bitrev(uint32_t k) { return __brev(k) >> (32
 
 // 2^R-point DIF network on x[base .. base + 2^R): stage t pairs (k, k + h),
 // h = 2^(R-t-1), twiddle w_{2^R}^((k mod h) 2^t); w_{2^R} = table[2^kLogTab / 2^R].
-template <int R, class F>
-__device__ __forceinline__ void small_dif(typename F::T *x, const typename F::W *__restrict__ tw, const F &f) {
+template <int R, class F, class Table>
+__device__ __forceinline__ void small_dif(typename F::T *x, const Table &tw, const F &f) {
 #pragma unroll
     for (int t = 0; t < R; ++t) {
         const int h = 1 << (R - t - 1);
@@ -148,8 +148,8 @@ __device__ __forceinline__ void small_dif(typename F::T *x, const typename F::W 
 
 // Inverse of small_dif up to the factor 2^R: stages in reverse order,
 // (a, b) -> (a + b w^-j, a - b w^-j).
-template <int R, class F>
-__device__ __forceinline__ void small_dit_inv(typename F::T *x, const typename F::W *__restrict__ itw, const F &f) {
+template <int R, class F, class Table>
+__device__ __forceinline__ void small_dit_inv(typename F::T *x, const Table &itw, const F &f) {
 #pragma unroll
     for (int t = R - 1; t >= 0; --t) {
         const int h = 1 << (R - t - 1);
@@ -970,62 +970,99 @@ hipError_t launch_bigmul_ntt64_list(const NttConst64 &K, const ListInst &src, ui
 // all of its entries before writing any).
 // ---------------------------------------------------------------------------
 
-// Two waves per (64 columns x, prime): the K-point column transforms of a
-// and b as their even (cyclic, H points; wave 0) and odd (negacyclic: inputs
-// times psi^i, psi of order K; wave 1) halves, pointwise Montgomery
-// products, H-point inverses, then through LDS the recombination
-// c_j = (E_j + psi^-j O_j) / K (wave 0), c_{j+H} = (E_j - psi^-j O_j) / K
-// (wave 1), and the scale that undoes the Montgomery factor and the row
-// transform's L.
+// The 2^R-th roots of the networks (powers below 2^(R - 1)) held in scalar
+// registers, indexed as the table they come from: each stage of a network
+// would otherwise wait for its own scalar loads, which miss at first touch.
 template <int R>
-__global__ __launch_bounds__(128) void ntt_col_kernel(NttConst K, uint32_t *__restrict__ tr, uint32_t L, uint32_t M,
+struct Roots {
+    static constexpr int kStep = kNttLogLmax - R, kCount = R ? 1 << (R - 1) : 1;
+    uint2 w[kCount];
+    __device__ __forceinline__ explicit Roots(const uint2 *__restrict__ tab) {
+#pragma unroll
+        for (int j = 0; j < kCount; ++j) w[j] = tab[uint32_t(j) << kStep];
+    }
+    __device__ __forceinline__ uint2 operator[](uint32_t e) const { return w[e >> kStep]; }
+};
+
+// Four waves per (64 columns x, prime): the K-point column transforms of a
+// and b as their even (cyclic, H points) and odd (negacyclic: inputs times
+// psi^i, psi of order K) halves, one wave each.  The waves of a half then swap
+// half of their results through LDS, so that each has H/2 positions of both
+// operands: pointwise Montgomery products, H/2-point inverse, and the factor
+// of the inverse's last stage; that stage, the recombination
+// c_j = (E_j + psi^-j O_j) / K, c_{j+H} = (E_j - psi^-j O_j) / K and the scale
+// that undoes the Montgomery factor and the row transform's L are done where
+// all four waves' results are read back, a quarter of the rows in each.
+// Bound by the 32-bit multiplies; two waves per column, each with both
+// operands, left the multiplier idle between dependent steps (2^22 / 2^24
+// bits 19.7 / 43.4 us, four waves 14.9 / 41.6).
+template <int R>
+__global__ __launch_bounds__(256) void ntt_col_kernel(NttConst K, uint32_t *__restrict__ tr, uint32_t L, uint32_t M,
                                                       uint32_t k) {
-    constexpr int H = 1 << R;
-    __shared__ uint32_t hsh[2][H * 64];  // E_j and psi^-j O_j of lane l at [64 j + l]
+    constexpr int H = 1 << R, H2 = R ? H / 2 : 1;  // R = 0: the waves of operand b end with the exchange
+    __shared__ uint32_t ex[2][2][H2 * 64];  // [half][wave that reads (first) and writes it (then)][64 i + lane]
     const uint32_t wgs_per_prime = L / 64;
     const int pr = int(blockIdx.x / wgs_per_prime);  // uniform: twiddles come through scalar loads
-    const uint32_t half = wave_in_block(), lane = lane_id();
+    const uint32_t wave = wave_in_block(), half = wave >> 1, op = wave & 1u, lane = lane_id();
     const uint32_t x = (blockIdx.x - uint32_t(pr) * wgs_per_prime) * 64 + lane;
     const uint32_t p = K.p[pr], pneg = K.pneg[pr];
     const Fp32 f{p};
     const uint2 *fw = K.fwd[pr], *iw = K.inv[pr];
-    const uint32_t *col = tr + x;
-    auto ld = [&](uint32_t slot) { return col[uint64_t(slot) * L]; };
-    uint32_t ya[H], yb[H];
+    const uint32_t *col = tr + x + (2 * op + uint32_t(pr)) * uint64_t(L);
+    // 2 x 32 roots at R = 6 are more than the scalar registers hold
+    using Table = std::conditional_t<(R < 6), Roots<R>, const uint2 *>;
+    const Table wf(fw), wi(iw);
+    uint32_t y[H], z[H2];
 #pragma unroll
-    for (int i = 0; i < H; ++i) {
-        ya[i] = uint32_t(i) < k ? ld(4 * i + pr) : 0u;
-        yb[i] = uint32_t(i) < k ? ld(4 * i + 2 + pr) : 0u;
-    }
+    for (int i = 0; i < H; ++i) y[i] = uint32_t(i) < k ? col[uint64_t(4 * i) * L] : 0u;
     if (half) {  // odd half: inputs twisted by psi^i (psi = w^(2^(14 - R)))
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            const uint2 ps = fw[uint32_t(i) << (14 - R)];
-            ya[i] = f.mulw(ya[i], ps);
-            yb[i] = f.mulw(yb[i], ps);
-        }
+        for (int i = 0; i < H; ++i) y[i] = f.mulw(y[i], fw[uint32_t(i) << (14 - R)]);
     }
-    small_dif<R>(ya, fw, f);
-    small_dif<R>(yb, fw, f);
+    small_dif<R>(y, wf, f);
+    // wave op goes on with positions [op H/2, (op + 1) H/2)
 #pragma unroll
-    for (int i = 0; i < H; ++i) ya[i] = mul_mont(ya[i], yb[i], p, pneg);
-    small_dit_inv<R>(ya, iw, f);
-    if (half) {
-#pragma unroll
-        for (int j = 0; j < H; ++j) ya[j] = f.mulw(ya[j], iw[uint32_t(j) << (14 - R)]);
+    for (int i = 0; i < H2; ++i) {
+        const uint32_t other = R == 0 ? y[i] : op ? y[i] : y[H - H2 + i];
+        z[i] = op ? y[H - H2 + i] : y[i];
+        ex[half][op ^ 1u][64 * i + lane] = other;
     }
-#pragma unroll
-    for (int j = 0; j < H; ++j) hsh[half][64 * j + lane] = ya[j];
     __syncthreads();
-    // recombine and scale by 2^-(R + 1 + M) 2^32; rows v < 2k - 1
+#pragma unroll
+    for (int i = 0; i < H2; ++i) z[i] = mul_mont(z[i], ex[half][op][64 * i + lane], p, pneg);
+    if constexpr (R > 1) small_dit_inv<R - 1>(z, wi, f);
+    if (R && op) {
+#pragma unroll
+        for (int i = 1; i < H2; ++i) z[i] = f.mulw(z[i], wi[uint32_t(i) << (15 - R)]);
+    }
+#pragma unroll
+    for (int i = 0; i < H2; ++i) ex[half][op][64 * i + lane] = z[i];
+    __syncthreads();
+    // rows v < 2k - 1; scale 2^-(R + 1 + M) 2^32
     const uint2 sc = make_uint2(K.scale[pr][R + 1 + M], K.scale_sh[pr][R + 1 + M]);
     const uint32_t nrows = 2 * k - 1;
-    uint32_t *out = tr + x;
+    uint32_t *out = tr + x + uint64_t(pr) * L;
+    auto put = [&](uint32_t v, uint32_t c) {
+        if (v < nrows) out[uint64_t(2 * v) * L] = f.mulw(c, sc);
+    };
 #pragma unroll
-    for (int j = 0; j < H; ++j) {
-        const uint32_t e = hsh[0][64 * j + lane], o = hsh[1][64 * j + lane];
-        const uint32_t v = uint32_t(j) + half * H;
-        if (v < nrows) out[uint64_t(2 * v + pr) * L] = f.mulw(half ? f.sub(e, o) : f.add(e, o), sc);
+    for (int i = 0; i < (H2 + 3) / 4; ++i) {
+        const uint32_t j = 4 * i + wave;
+        if (j >= uint32_t(H2)) break;
+        const uint32_t le = ex[0][0][64 * j + lane], lo = ex[1][0][64 * j + lane];
+        if constexpr (R == 0) {
+            put(0, f.add(le, lo));
+            put(1, f.sub(le, lo));
+        } else {
+            const uint32_t ue = ex[0][1][64 * j + lane], uo = ex[1][1][64 * j + lane];
+            const uint32_t e0 = f.add(le, ue), e1 = f.sub(le, ue);
+            const uint32_t o0 = f.mulw(f.add(lo, uo), iw[j << (14 - R)]);
+            const uint32_t o1 = f.mulw(f.sub(lo, uo), iw[(j + H2) << (14 - R)]);
+            put(j, f.add(e0, o0));
+            put(j + H2, f.add(e1, o1));
+            put(j + H, f.sub(e0, o0));
+            put(j + H + H2, f.sub(e1, o1));
+        }
     }
 }
 
@@ -1056,7 +1093,151 @@ __global__ __launch_bounds__((1 << M) / E) void ntt_rowinv_kernel(NttConst K, ui
     }
 }
 
-// Coefficient P (16-bit position) of the long product from the product rows.
+// The row transforms cut into halves, one workgroup of half the threads per
+// (block, operand, prime, half) and per (product row, prime, half): a product
+// has too few rows for the chip otherwise (128 and 126 workgroups at 2^22
+// bits).  The halves are the even (h = 0) and odd (h = 1) frequencies, which
+// the first DIF stage of the full-length transform separates; a block fills
+// at most the lower half of its row (L >= 4 bw coefficients of which 2 bw are
+// there), so that stage needs no sums: half h of pass 0 takes the group's
+// 2^R inputs as they are, times w^k (w of order 2^(R + 1)) in the odd half.
+// From there on it is the full transform's own second half or first half,
+// with its pass tables and its bit-reversed positions [h L/2, (h + 1) L/2).
+//
+// A half's chain of dependent steps bounds the kernel (one wave per SIMD at
+// 2^22 bits), so it has one trip to memory: coefficients and the twiddles of
+// both passes are loaded at the start, and no barrier stands between a
+// thread's own reads and writes of the same LDS words.  Forward / inverse rows
+// of one 2^22-bit product 21.5 / 20.3 us as whole rows (512 threads) -> 17.4 /
+// 14.1 us; of 2^19 bits 13.1 / 11.9 -> 9.5 / 8.6; at 2^24 bits, where whole
+// rows fill the chip, 39 either way.
+template <int M>
+struct RowHalf {
+    static constexpr int R = M - 11;          // stages of a half's pass 0
+    static constexpr int G = E >> R;          // its groups of 2^R points per thread
+    static constexpr uint32_t T = (1u << M) / (2 * E);
+    static constexpr size_t kLds = sizeof(uint32_t) * ((1u << (M - 1)) + (1u << (M - 1)) / 32);
+    // pass-0 twiddles of the thread's groups: row bitrev_(R+1)(h 2^R + k)
+    static __device__ __forceinline__ void load_pass0(uint2 (&w)[E], const uint2 *__restrict__ tab, uint32_t h) {
+        const uint2 *t0 = tab + Fp32::t0(M) + 1024 * h + threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < E; ++i) w[i] = t0[2048 * bitrev_of(i & ((1 << R) - 1)) + T * (i >> R)];
+    }
+    static __device__ __forceinline__ void load_pass1(uint2 (&w)[E], const uint2 *__restrict__ tab) {
+        const uint2 *t1 = tab + Fp32::kT1 + (threadIdx.x & 31u);
+#pragma unroll
+        for (int k = 0; k < E; ++k) w[k] = t1[32 * bitrev<5>(uint32_t(k))];
+    }
+    static __device__ __forceinline__ uint32_t bitrev_of(int k) {
+        if constexpr (R == 0) return 0;
+        else return bitrev<R>(uint32_t(k));
+    }
+};
+
+template <int M>
+__global__ __launch_bounds__(RowHalf<M>::T) void ntt_rowfwd_half_kernel(NttConst K, BlockInst src,
+                                                                        uint32_t *__restrict__ tr) {
+    extern __shared__ __align__(16) uint32_t sh[];
+    using H = RowHalf<M>;
+    constexpr int R = H::R;
+    const uint32_t work = blockIdx.x >> 1, h = blockIdx.x & 1u, t = threadIdx.x;  // grid 8 k
+    const InstRef in = src.get(work >> 2);
+    const int pr = int(work & 1u);
+    const uint16_t *coef = reinterpret_cast<const uint16_t *>((work & 2u) ? in.b : in.a);
+    const uint32_t ncoef = 2 * in.n;
+    const Roots<5> fw(K.fwd[pr]);
+    const Fp32 f{K.p[pr]};
+    uint32_t x[E];
+    uint2 w0[E], w1[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const uint32_t c = t + H::T * (i >> R) + (uint32_t(i & ((1 << R) - 1)) << 10);
+        x[i] = c < ncoef ? coef[c] : 0u;
+    }
+    H::load_pass0(w0, K.fwd[pr], h);
+    H::load_pass1(w1, K.fwd[pr]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (h) {
+#pragma unroll
+        for (int i = 0; i < E; ++i)
+            if (const int k = i & ((1 << R) - 1)) x[i] = f.mulw(x[i], fw[uint32_t(k) << (kNttLogLmax - R - 1)]);
+    }
+#pragma unroll
+    for (int g = 0; g < H::G; ++g) small_dif<R>(x + (g << R), fw, f);
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+        sh[padx(t + H::T * (i >> R)) + 1056 * (i & ((1 << R) - 1))] = f.mulw(x[i], w0[i]);
+    __syncthreads();
+    uint32_t *q = sh + base_pass1(t);
+#pragma unroll
+    for (int k = 0; k < E; ++k) x[k] = q[33 * k];
+    small_dif<5>(x, fw, f);
+#pragma unroll
+    for (int k = 0; k < E; ++k) q[33 * k] = k ? f.mulw(x[k], w1[k]) : x[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < E; ++k) x[k] = sh[33 * t + k];
+    small_dif<5>(x, fw, f);
+    uint4 *dst = reinterpret_cast<uint4 *>(tr + (uint64_t(work) << M) + (h << (M - 1)) + E * t);
+#pragma unroll
+    for (int v = 0; v < E / 4; ++v) dst[v] = make_uint4(x[4 * v], x[4 * v + 1], x[4 * v + 2], x[4 * v + 3]);
+}
+
+// The inverse's halves z_0 and z_1 (the latter already times w_L^-j), each in
+// place; their sum and difference are the row's lower and upper half
+// (LargeCoef).  The column kernel applied every scale factor.
+template <int M>
+__global__ __launch_bounds__(RowHalf<M>::T) void ntt_rowinv_half_kernel(NttConst K, uint32_t *__restrict__ tr) {
+    extern __shared__ __align__(16) uint32_t sh[];
+    using H = RowHalf<M>;
+    constexpr int R = H::R;
+    const uint32_t slot = blockIdx.x >> 1, h = blockIdx.x & 1u, t = threadIdx.x;  // grid 2 (rows of both primes)
+    const int pr = int(slot & 1u);
+    uint32_t *row = tr + (uint64_t(slot) << M) + (h << (M - 1));
+    const Roots<5> iw(K.inv[pr]);
+    const Fp32 f{K.p[pr]};
+    uint32_t x[E];
+    uint2 w0[E], w1[E];
+    const uint4 *src = reinterpret_cast<const uint4 *>(row + E * t);
+#pragma unroll
+    for (int v = 0; v < E / 4; ++v) {
+        const uint4 u = src[v];
+        x[4 * v] = u.x;
+        x[4 * v + 1] = u.y;
+        x[4 * v + 2] = u.z;
+        x[4 * v + 3] = u.w;
+    }
+    H::load_pass1(w1, K.inv[pr]);
+    H::load_pass0(w0, K.inv[pr], h);
+    __builtin_amdgcn_sched_barrier(0);
+    small_dit_inv<5>(x, iw, f);
+#pragma unroll
+    for (int k = 0; k < E; ++k) sh[33 * t + k] = x[k];
+    __syncthreads();  // also: every thread has read its part of the row
+    uint32_t *q = sh + base_pass1(t);
+#pragma unroll
+    for (int k = 0; k < E; ++k) x[k] = k ? f.mulw(q[33 * k], w1[k]) : q[0];
+    small_dit_inv<5>(x, iw, f);
+#pragma unroll
+    for (int k = 0; k < E; ++k) q[33 * k] = x[k];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+        x[i] = f.mulw(sh[padx(t + H::T * (i >> R)) + 1056 * (i & ((1 << R) - 1))], w0[i]);
+#pragma unroll
+    for (int g = 0; g < H::G; ++g) small_dit_inv<R>(x + (g << R), iw, f);
+    if (h) {
+#pragma unroll
+        for (int i = 0; i < E; ++i)
+            if (const int k = i & ((1 << R) - 1)) x[i] = f.mulw(x[i], iw[uint32_t(k) << (kNttLogLmax - R - 1)]);
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) row[t + H::T * (i >> R) + (uint32_t(i & ((1 << R) - 1)) << 10)] = x[i];
+}
+
+// Coefficient P (16-bit position) of the long product from the product rows;
+// with SPLIT from their halves (ntt_rowinv_half_kernel).
+template <bool SPLIT>
 struct LargeCoef {
     const uint32_t *tr;
     uint32_t L, bw2, nrows;  // bw2 = 2 bw coefficients per block; nrows = 2k - 1
@@ -1065,6 +1246,21 @@ struct LargeCoef {
     __device__ __forceinline__ uint32_t crt1(uint32_t r1, uint32_t r2) const {
         return mul_shoup(sub_mod(r2, r1, p2), crt, crt_sh, p2);
     }
+    // Positions k .. k + 3 (k a multiple of 4) of one row.
+    __device__ __forceinline__ void residues(uint32_t slot, uint32_t k, uint32_t p, uint32_t (&r)[4]) const {
+        const uint32_t *row = tr + uint64_t(slot) * L;
+        if constexpr (SPLIT) {
+            const uint32_t half = L / 2, j = k & (half - 1);
+            const uint4 e = *reinterpret_cast<const uint4 *>(row + j);
+            const uint4 o = *reinterpret_cast<const uint4 *>(row + half + j);
+            const uint32_t ev[4] = {e.x, e.y, e.z, e.w}, ov[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = add_mod(ev[i], k < half ? ov[i] : p - ov[i], p);
+        } else {
+            const uint4 e = *reinterpret_cast<const uint4 *>(row + k);
+            r[0] = e.x; r[1] = e.y; r[2] = e.z; r[3] = e.w;
+        }
+    }
     // Coefficients P .. P + 3 (P a multiple of 4; bw2 is one too, so they lie
     // in one block row): four rows' reads at once, at clamped rows where a
     // term is absent (the scratch holds 4 k >= 2 nrows + 2 rows).
@@ -1072,12 +1268,11 @@ struct LargeCoef {
         const uint32_t v = P / bw2, u = P - v * bw2;
         const bool t0 = v < nrows, t1 = v >= 1 && v - 1 < nrows;
         const uint32_t va = t0 ? v : 0u, vb = t1 ? v - 1 : 0u;
-        const uint4 a1 = *reinterpret_cast<const uint4 *>(tr + uint64_t(2 * va) * L + u);
-        const uint4 a2 = *reinterpret_cast<const uint4 *>(tr + uint64_t(2 * va + 1) * L + u);
-        const uint4 b1 = *reinterpret_cast<const uint4 *>(tr + uint64_t(2 * vb) * L + u + bw2);
-        const uint4 b2 = *reinterpret_cast<const uint4 *>(tr + uint64_t(2 * vb + 1) * L + u + bw2);
-        const uint32_t x1[4] = {a1.x, a1.y, a1.z, a1.w}, x2[4] = {a2.x, a2.y, a2.z, a2.w};
-        const uint32_t y1[4] = {b1.x, b1.y, b1.z, b1.w}, y2[4] = {b2.x, b2.y, b2.z, b2.w};
+        uint32_t x1[4], x2[4], y1[4], y2[4];
+        residues(2 * va, u, p1, x1);
+        residues(2 * va + 1, u, p2, x2);
+        residues(2 * vb, u + bw2, p1, y1);
+        residues(2 * vb + 1, u + bw2, p2, y2);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const uint64_t ca = uint64_t(p1) * crt1(x1[e], x2[e]) + x1[e];
@@ -1091,14 +1286,18 @@ struct LargeCoef {
 // < 2^70, written lo_w + m_w 2^32 (m_w < 2^38).  Then
 //     product = sum_w S_w 2^(32 w),  S_w = lo_w + (m_{w-1} mod 2^32) + floor(m_{w-2} / 2^32) < 2^34,
 // stored as the low words Lw[w] = S_w mod 2^32 and high words Hw[w + 1] =
-// floor(S_w / 2^32) for the final addition.  One thread per 8 words w0 ..
-// w0 + 7: it reads coefficients 2 w0 - 8 .. 2 w0 + 15 (six groups of four,
-// all issued before use) and recomputes the words below its group, so both
-// of its output runs, Lw[w0 ..] and Hw[w0 ..], are aligned 8-word stores.
-// A workgroup covers one tile of kLargeTileWords words and also records how
-// the tile's part of Lw + Hw passes a carry (the status read by
-// large_ntt_add_kernel): bit 0 = it carries out by itself, bit 1 = every
-// word of its sum is all-ones (it carries out exactly when a carry comes in).
+// floor(S_w / 2^32) for the final addition.  A lane takes four coefficients
+// (two words) at a time, the lanes of a wave consecutive ones, so that reads
+// and writes are whole lines; what a word needs of the two words below comes
+// from the lane below, and the first lane's from the wave's previous round or,
+// before its first, from two groups read ahead of it.  A workgroup covers one
+// tile of kLargeTileWords words and also records how the tile's part of
+// Lw + Hw passes a carry (the status read by large_ntt_add_kernel): bit 0 =
+// it carries out by itself, bit 1 = every word of its sum is all-ones (it
+// carries out exactly when a carry comes in).  Eight words per thread, with
+// their 16-byte reads 64 bytes apart, refetched every line from L2: twice the
+// streams that halved rows have took 11 / 59 us at 2^22 / 2^24 bits, whole
+// lines take 6.5 / 13.5.
 constexpr uint32_t kLargeTileWords = 8 * 256;
 
 // Tile status from the threads' 8-word sums (carry out g, all-ones p), and
@@ -1132,64 +1331,73 @@ __device__ __forceinline__ uint32_t fold_sum8(const uint32_t (&lw)[8], const uin
     return g;
 }
 
-__global__ __launch_bounds__(256) void large_ntt_fold_kernel(LargeCoef coef, uint64_t nwords, uint32_t *__restrict__ Lw,
-                                                             uint32_t *__restrict__ Hw, uint8_t *__restrict__ status) {
-    __shared__ uint32_t summary[4];
-    const uint64_t ngroups = (nwords + 7) / 8, ntiles = (nwords + kLargeTileWords - 1) / kLargeTileWords;
-    const uint32_t pmax = uint32_t(2 * nwords - 4);  // last group of four coefficients
-    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const uint64_t g = tile * 256 + threadIdx.x;
-        const bool act = g < ngroups;
-        const uint64_t w0 = 8 * g;
-        uint64_t cf[24];  // coefficient 2 w0 - 8 + i
+constexpr uint32_t kFoldThreads = 512;
+constexpr int kFoldRounds = kLargeTileWords / (2 * kFoldThreads);
+
+template <bool SPLIT>
+__global__ __launch_bounds__(kFoldThreads) void large_ntt_fold_kernel(LargeCoef<SPLIT> coef, uint64_t nwords,
+                                                                      uint32_t *__restrict__ Lw,
+                                                                      uint32_t *__restrict__ Hw,
+                                                                      uint8_t *__restrict__ status) {
+    constexpr uint32_t kWaves = kFoldThreads / 64;
+    __shared__ uint32_t summary[kWaves];
+    const uint32_t ngroups = uint32_t(nwords / 2), ntiles = uint32_t((nwords + kLargeTileWords - 1) / kLargeTileWords);
+    const uint32_t lane = lane_id(), wave = wave_in_block();
+    // v of the lane below, `first` in lane 0
+    auto below = [](uint32_t v, uint32_t first) {
+        return uint32_t(__builtin_amdgcn_update_dpp(int(first), int(v), 0x138 /* wave_shr:1 */, 0xf, 0xf, false));
+    };
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const uint32_t g0 = tile * (kLargeTileWords / 2) + wave * (64 * kFoldRounds) + lane;
+        // round 0 reads the two groups below the wave's own (lanes 62, 63)
+        uint64_t cf[kFoldRounds + 1][4];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            const int64_t P = int64_t(2 * w0) - 8 + 4 * q;
-            const bool ok = act && P >= 0 && P <= int64_t(pmax);
+        for (int i = 0; i <= kFoldRounds; ++i) {
+            const uint32_t g = g0 + 64 * i - 64;  // below 0: wraps, so not < ngroups
+            const bool ok = g < ngroups && (i > 0 || lane >= 62);
             uint64_t c4[4];
-            coef.four(ok ? uint32_t(P) : 0u, c4);
+            coef.four(ok ? 4 * g : 0u, c4);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) cf[4 * q + e] = ok ? c4[e] : 0ull;
+            for (int e = 0; e < 4; ++e) cf[i][e] = ok ? c4[e] : 0ull;
         }
-        // words w0 - 4 + i, i < 12
-        uint32_t lo[12];
-        uint64_t m[12];
+        uint32_t fa = 0, fb = 0, fh = 0, tg = 0, tp = 1;
 #pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            const uint64_t c0 = cf[2 * i], c1 = cf[2 * i + 1];
-            const uint64_t t = c0 + ((c1 & 0xFFFFu) << 16);  // < 2^53 + 2^32
-            lo[i] = uint32_t(t);
-            m[i] = (t >> 32) + (c1 >> 16);
+        for (int i = 0; i <= kFoldRounds; ++i) {
+            const uint64_t t0 = cf[i][0] + ((cf[i][1] & 0xFFFFu) << 16), t1 = cf[i][2] + ((cf[i][3] & 0xFFFFu) << 16);
+            const uint64_t m0 = (t0 >> 32) + (cf[i][1] >> 16), m1 = (t1 >> 32) + (cf[i][3] >> 16);  // < 2^38
+            const uint32_t a = uint32_t(m1), b = uint32_t(m1 >> 32) | (uint32_t(m0 >> 32) << 8);
+            const uint32_t ba = below(a, fa), bb = below(b, fb);
+            const uint64_t S0 = uint64_t(uint32_t(t0)) + ba + (bb >> 8);
+            const uint64_t S1 = uint64_t(uint32_t(t1)) + uint32_t(m0) + (bb & 255u);
+            const uint32_t h1 = uint32_t(S0 >> 32), h2 = uint32_t(S1 >> 32), h0 = below(h2, fh);
+            fa = __builtin_amdgcn_readlane(a, 63);
+            fb = __builtin_amdgcn_readlane(b, 63);
+            fh = __builtin_amdgcn_readlane(h2, 63);
+            if (i == 0) continue;
+            const uint32_t g = g0 + 64 * i - 64;
+            const bool act = g < ngroups;  // words at or above nwords are zero (the product has nwords words)
+            const uint64_t l = uint32_t(S0) | (S1 << 32), hh = h0 | (uint64_t(h1) << 32), sum = l + hh;
+            if (act) {
+                *reinterpret_cast<uint64_t *>(Lw + 2 * g) = l;
+                *reinterpret_cast<uint64_t *>(Hw + 2 * g) = hh;
+            }
+            const uint64_t P = ballot(act && sum == ~0ull);
+            const WaveCarry wc = wave_carry(ballot(act && sum < l), P, 0);
+            tg = wc.out | (P == ~0ull ? tg : 0u);
+            tp &= P == ~0ull ? 1u : 0u;
         }
-        // S_w for w = w0 - 1 + j, j < 9 (i = j + 3)
-        uint64_t S[9];
+        if (lane == 0) summary[wave] = tg | (tp << 1);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            tg = 0, tp = 1;
 #pragma unroll
-        for (int j = 0; j < 9; ++j) S[j] = uint64_t(lo[j + 3]) + uint32_t(m[j + 2]) + (m[j + 1] >> 32);
-        uint32_t lw[8], hw[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            lw[j] = uint32_t(S[j + 1]);
-            hw[j] = w0 + uint64_t(j) >= 1 ? uint32_t(S[j] >> 32) : 0u;  // Hw[w] = floor(S_(w-1) / 2^32), Hw[0] = 0
+            for (uint32_t v = 0; v < kWaves; ++v) {
+                tg = (summary[v] & 1u) | ((summary[v] >> 1) & tg);
+                tp &= summary[v] >> 1;
+            }
+            status[tile] = uint8_t(tg | (tp << 1));
         }
-        if (act && w0 + 8 <= nwords) {
-            uint4 *pl = reinterpret_cast<uint4 *>(Lw + w0), *ph = reinterpret_cast<uint4 *>(Hw + w0);
-            pl[0] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-            pl[1] = make_uint4(lw[4], lw[5], lw[6], lw[7]);
-            ph[0] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-            ph[1] = make_uint4(hw[4], hw[5], hw[6], hw[7]);
-        } else if (act) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (w0 + uint64_t(j) < nwords) {
-                    Lw[w0 + j] = lw[j];
-                    Hw[w0 + j] = hw[j];
-                }
-        }
-        // words at or above nwords are zero (the product has nwords words)
-        uint32_t sm[8];
-        bool ones = false;
-        const uint32_t gc = fold_sum8(lw, hw, sm, ones);
-        (void)tile_carries(act ? gc : 0u, act && ones, 0u, summary, threadIdx.x == 0 ? status + tile : nullptr);
+        __syncthreads();  // summary is free again
     }
 }
 
@@ -1273,20 +1481,38 @@ LargeNttLayout large_ntt_layout(uint64_t n32, uint32_t bw) {
     return s;
 }
 
+// Rows are cut into halves from M = 12 on (transforms start at 2^11 points):
+// faster at every larger length, or equal where whole rows fill the chip.
+constexpr bool rows_split(uint32_t M) { return M > kNttLogLmin; }
+
 template <int M>
 hipError_t launch_large_rows(const NttConst &K, const BlockInst &src, uint32_t *tr, uint32_t nslots_inv, bool fwd,
                              hipStream_t st) {
-    const size_t lds = sizeof(uint32_t) * ((1u << M) + (1u << M) / 32);
+    constexpr bool split = rows_split(M);
     static std::atomic<uint64_t> lds_set[2];
-    const void *fn = fwd ? reinterpret_cast<const void *>(&ntt_fwd_kernel<M, BlockInst>)
-                         : reinterpret_cast<const void *>(&ntt_rowinv_kernel<M>);
-    hipError_t e = lds_limit_once(fn, lds_set[fwd ? 0 : 1]);
-    if (e != hipSuccess) return e;
-    const uint32_t T = (1u << M) / E;
-    if (fwd)
-        hipLaunchKernelGGL((ntt_fwd_kernel<M, BlockInst>), dim3(4 * src.k), dim3(T), lds, st, K, src, 0, src.k, tr);
-    else
-        hipLaunchKernelGGL((ntt_rowinv_kernel<M>), dim3(nslots_inv), dim3(T), lds, st, K, tr, nslots_inv);
+    if constexpr (split) {
+        constexpr size_t lds = RowHalf<M>::kLds;
+        constexpr uint32_t T = RowHalf<M>::T;
+        const void *fn = fwd ? reinterpret_cast<const void *>(&ntt_rowfwd_half_kernel<M>)
+                             : reinterpret_cast<const void *>(&ntt_rowinv_half_kernel<M>);
+        hipError_t e = lds_limit_once(fn, lds_set[fwd ? 0 : 1]);
+        if (e != hipSuccess) return e;
+        if (fwd)
+            hipLaunchKernelGGL((ntt_rowfwd_half_kernel<M>), dim3(8 * src.k), dim3(T), lds, st, K, src, tr);
+        else
+            hipLaunchKernelGGL((ntt_rowinv_half_kernel<M>), dim3(2 * nslots_inv), dim3(T), lds, st, K, tr);
+    } else {
+        constexpr size_t lds = sizeof(uint32_t) * ((1u << M) + (1u << M) / 32);
+        constexpr uint32_t T = (1u << M) / E;
+        const void *fn = fwd ? reinterpret_cast<const void *>(&ntt_fwd_kernel<M, BlockInst>)
+                             : reinterpret_cast<const void *>(&ntt_rowinv_kernel<M>);
+        hipError_t e = lds_limit_once(fn, lds_set[fwd ? 0 : 1]);
+        if (e != hipSuccess) return e;
+        if (fwd)
+            hipLaunchKernelGGL((ntt_fwd_kernel<M, BlockInst>), dim3(4 * src.k), dim3(T), lds, st, K, src, 0, src.k, tr);
+        else
+            hipLaunchKernelGGL((ntt_rowinv_kernel<M>), dim3(nslots_inv), dim3(T), lds, st, K, tr, nslots_inv);
+    }
     return hipGetLastError();
 }
 
@@ -1304,7 +1530,7 @@ hipError_t launch_rows(uint32_t M, const NttConst &K, const BlockInst &src, uint
 
 hipError_t launch_cols(uint32_t R, const NttConst &K, uint32_t *tr, uint32_t M, uint32_t k, hipStream_t st) {
     const uint32_t L = 1u << M;
-    const dim3 grid(2 * L / 64), blk(128);
+    const dim3 grid(2 * L / 64), blk(256);
     switch (R) {
         case 0: hipLaunchKernelGGL((ntt_col_kernel<0>), grid, blk, 0, st, K, tr, L, M, k); break;
         case 1: hipLaunchKernelGGL((ntt_col_kernel<1>), grid, blk, 0, st, K, tr, L, M, k); break;
@@ -1322,8 +1548,9 @@ hipError_t launch_cols(uint32_t R, const NttConst &K, uint32_t *tr, uint32_t M, 
 
 // Blocks of 2^(11..13) words: the smallest that gives at most 32 blocks (64
 // at 8192 words).  Measured on one product each (MI355X): 2^19 / 2^20 bits
-// fastest with 2048-word blocks (58 / 66 us against 76 / 103 with 512-word
-// ones), 2^22 bits with 4096 (104 against 120 with 2048 and 111 with 8192).
+// 28.6 / 31.4 us with 2048-word blocks (35 / 46 with 512-word ones, 32 / 35
+// with 4096), 2^22 bits 52 with 4096 (63 with 2048, 60 with 8192), 2^23 bits
+// 75 with 8192 (86 with 4096).
 uint32_t large_ntt_auto_block(uint64_t n32) {
     uint32_t bw = 2048;
     while (bw < kMaxLimbs32 && (n32 + bw - 1) / bw > kLargeNttMaxBlocks / 2) bw *= 2;
@@ -1350,9 +1577,14 @@ hipError_t launch_bigmul_large_ntt(const Ctx &c, const uint32_t *a, const uint32
     // derived from the statuses below it
     const uint64_t nwords = 2 * n32, ntiles = (nwords + kLargeTileWords - 1) / kLargeTileWords;
     auto *status = scratch + s.st;
-    const LargeCoef coef{tr, 1u << s.M, 2 * bw, nrows, K.p[0], K.p[1], K.crt, K.crt_sh};
     const uint32_t grid = uint32_t(std::min<uint64_t>(ntiles, 65536));
-    hipLaunchKernelGGL(large_ntt_fold_kernel, dim3(grid), dim3(256), 0, st, coef, nwords, Lw, Hw, status);
+    if (rows_split(s.M)) {
+        const LargeCoef<true> coef{tr, 1u << s.M, 2 * bw, nrows, K.p[0], K.p[1], K.crt, K.crt_sh};
+        hipLaunchKernelGGL(large_ntt_fold_kernel<true>, dim3(grid), dim3(kFoldThreads), 0, st, coef, nwords, Lw, Hw, status);
+    } else {
+        const LargeCoef<false> coef{tr, 1u << s.M, 2 * bw, nrows, K.p[0], K.p[1], K.crt, K.crt_sh};
+        hipLaunchKernelGGL(large_ntt_fold_kernel<false>, dim3(grid), dim3(kFoldThreads), 0, st, coef, nwords, Lw, Hw, status);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(large_ntt_add_kernel, dim3(grid), dim3(256), 0, st, Lw, Hw, status, out, uint32_t(nwords));

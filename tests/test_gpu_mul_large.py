@@ -180,3 +180,22 @@ def test_max_size_sampled(B, ctx, orc):
     assert (got[:BLOCK] == low).all()
     for p in ((1 << 61) - 1, (1 << 61) - 31, 2305843009213693921):
         assert _mod(got, p) == _mod(a, p) * _mod(b, p) % p, p
+
+
+@pytest.mark.parametrize("block_bits", [1 << 14, 1 << 15, 1 << 17])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 8, 9, 16, 17, 33])
+def test_ntt_rows_and_columns(B, ctx, orc, k, block_bits):
+    """Whole (2^14-bit blocks) and halved rows over every column length, a
+    ragged last block, operands and result one word off a 16-byte boundary."""
+    bw = block_bits // 32
+    n = (k - 1) * bw + max(1, bw // 3)
+    if n > 40000 or (block_bits == 1 << 17 and k > 5):
+        pytest.skip("the smaller blocks cover this column length")
+    rng = np.random.default_rng(k)
+    a, b = rng.integers(0, 2**32, (2, n), dtype=np.uint64).astype(np.uint32)
+    da, db = (G.to_dev(np.concatenate([[0], v]).astype(np.uint32))[1:] for v in (a, b))
+    out = G.empty_dev((2 * n + 1,), np.uint32)[1:]
+    B.bigmul_large(ctx, da, db, out, algo=0, block_bits=block_bits)
+    G.sync()
+    bad = np.nonzero(G.from_dev(out, np.uint32) != orc.mul(a[None, :], b[None, :])[0])[0]
+    assert bad.size == 0, f"{bad.size} limbs differ, first at {bad[:8]}"
