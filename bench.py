@@ -681,13 +681,25 @@ def cpu_baseline_stream(args, a, b, off, nn):
                          "u32_macs_per_s": macs1 / secs1, "sample": "first 64 pairs of the stream, once"}}
 
 
+def low_roofline(n32, macs, us):
+    """Roofline of low products (Poly: four of them) of `macs` 32-bit terms in
+    all: the int8 matrix rate (16 byte products a term) above 32 words, the
+    VALU's below."""
+    if n32 <= 32:
+        ach, peak, bound, unit = macs / (us * 1e-6), VALU_MAC_PEAK, "alu", "T u32-MAC/s"
+    else:
+        ach, peak, bound, unit = 32.0 * macs / (us * 1e-6), MFMA_I8_PEAK_OPS, "mfma", "TOP/s (int8)"
+    return {"bound": bound, "achieved": round(ach / 1e12, 3), "peak": round(peak / 1e12, 3), "unit": unit,
+            "frac": round(ach / peak, 4)}
+
+
 def bench_fused(args):
     """The paper's fused programs (Section 6.1) over the addition sweep's
     batches (NumBits x NumInsts = 2^32, u64 limbs): 1-Add (bigadd), 6-Add,
     Poly and the same-length product 1-Mul (Figs. 4-5), one launch each.  6-Add is memory-bound: 3 N/8 bytes per instance
     (two operands in, one result out) against HBM.  Poly is four same-length
-    VALU products of n (n + 1) / 2 u32 terms each (n 32-bit words) against the
-    VALU multiply-accumulate peak."""
+    products of n (n + 1) / 2 u32 terms each (n 32-bit words), see
+    low_roofline."""
     import torch
 
     import paper_2405_14642_amd as B
@@ -739,12 +751,8 @@ def bench_fused(args):
             "add6_hbm_frac": round(gbs / HBM_PEAK_GBS, 4), "poly_us": round(usp, 2),
             "poly_u32_macs_per_s": macs / (usp * 1e-6), "mul_low_us": round(usm, 2),
             "poly_over_mul_low": round(usp / usm, 3),
-            "mul_low_roofline": {"bound": "alu", "achieved": round(macs / 4 / (usm * 1e-6) / 1e12, 3),
-                                 "peak": round(VALU_MAC_PEAK / 1e12, 3), "unit": "T u32-MAC/s",
-                                 "frac": round(macs / 4 / (usm * 1e-6) / VALU_MAC_PEAK, 4)},
-            "poly_roofline": {"bound": "alu", "achieved": round(macs / (usp * 1e-6) / 1e12, 3),
-                              "peak": round(VALU_MAC_PEAK / 1e12, 3), "unit": "T u32-MAC/s",
-                              "frac": round(macs / (usp * 1e-6) / VALU_MAC_PEAK, 4)}}
+            "mul_low_roofline": low_roofline(n32, macs / 4, usm),
+            "poly_roofline": low_roofline(n32, macs, usp)}
         add6_s += us6 * 1e-6
         poly_s += usp * 1e-6
         insts += batch
