@@ -37,24 +37,44 @@ constexpr int kPackedQ = 2;  // output words per lane of the packed kernels
 
 namespace {
 
-// A lane's 4-word chunk c of an n-word operand (zero past n or when invalid).
-__device__ __forceinline__ void load_chunk(const uint32_t *p, uint32_t n, uint32_t c, bool valid, uint32_t (&x)[4]) {
-    const uint32_t base = 4 * c;
-    if (valid && base + 4 <= n && (reinterpret_cast<uintptr_t>(p + base) & 15) == 0) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(p + base);
-        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = (valid && base + t < n) ? p[base + t] : 0u;
+typedef u32x4 __attribute__((aligned(4))) u32x4_word;  // 16 bytes at any word address
+
+// A lane's 4-word chunk c of an n-word operand in two steps, so that all of a
+// lane's loads are in flight before the first is used (a branch for the ragged
+// chunk at each load made every load wait for the one before it): the 16 bytes
+// at the chunk, or the operand's last 16 where the chunk ends past it (n >= 4),
+// then the words moved into place, zero past n or when not valid.
+template <bool NT>
+__device__ __forceinline__ u32x4 load_raw(const uint32_t *p, uint32_t n, uint32_t c) {
+    const u32x4_word *q = reinterpret_cast<const u32x4_word *>(p + min(4 * c, n - 4));
+    return NT ? __builtin_nontemporal_load(q) : *q;
+}
+__device__ __forceinline__ void place_words(const u32x4 &v, uint32_t n, uint32_t c, bool valid, uint32_t (&x)[4]) {
+    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    if (n & 3u) {
+        const uint32_t s = 4 * c + 4 > n ? 4 * c + 4 - n : 0u;  // words of the chunk past n
+        if (s & 1u) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; x[3] = 0; }
+        if (s & 2u) { x[0] = x[2]; x[1] = x[3]; x[2] = 0; x[3] = 0; }
     }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) x[t] = valid ? x[t] : 0u;
+}
+
+// Operands of fewer than 4 words.
+__device__ __forceinline__ void load_short(const uint32_t *p, uint32_t n, bool valid, uint32_t (&x)[4]) {
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) x[t] = valid && t < n ? p[t] : 0u;
 }
 
 // Stores the words of chunk c below n when valid.
+template <bool NT>
 __device__ __forceinline__ void store_chunk(uint32_t *p, uint32_t n, uint32_t c, bool valid, const uint32_t (&x)[4]) {
     if (!valid) return;
     const uint32_t base = 4 * c;
-    if (base + 4 <= n && (reinterpret_cast<uintptr_t>(p + base) & 15) == 0) {
-        *reinterpret_cast<uint4 *>(p + base) = make_uint4(x[0], x[1], x[2], x[3]);
+    if (base + 4 <= n) {
+        const u32x4 v = {x[0], x[1], x[2], x[3]};
+        u32x4_word *q = reinterpret_cast<u32x4_word *>(p + base);
+        if (NT) __builtin_nontemporal_store(v, q); else *q = v;
     } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -64,10 +84,12 @@ __device__ __forceinline__ void store_chunk(uint32_t *p, uint32_t n, uint32_t c,
 
 }  // namespace
 
-// Instances of up to 256 words (64 chunks): 64 / 2^seg_log instances per
-// wave, lane j of segment s holding chunk j of instance s.  `keep` masks the
-// lanes whose carry may reach the next lane: not an instance's last chunk
-// (its carry out is dropped, mod 2^N) and not past the instance's end.
+// Instances of up to 256 words (64 chunks): 64 / 2^seg_log instances per row,
+// ROWS rows per wave, lane j of segment s holding chunk j of instance s.
+// `keep` masks the lanes whose carry may reach the next lane: not an
+// instance's last chunk (its carry out is dropped, mod 2^N) and not past the
+// instance's end.
+template <int ROWS, bool NTL, bool NTS>
 __global__ __launch_bounds__(256) void fused_add6_packed_kernel(const uint32_t *__restrict__ a,
                                                                 const uint32_t *__restrict__ b,
                                                                 uint32_t *__restrict__ out, uint32_t n,
@@ -75,30 +97,53 @@ __global__ __launch_bounds__(256) void fused_add6_packed_kernel(const uint32_t *
     const uint32_t lane = lane_id(), wave = wave_in_block();
     const uint32_t nchunks = (n + 3) / 4, ipw = 64u >> seg_log;
     const uint32_t j = lane & ((1u << seg_log) - 1u);
-    for (uint64_t g = uint64_t(blockIdx.x) * 4 + wave; g * ipw < batch; g += uint64_t(gridDim.x) * 4) {
-        const uint64_t inst = g * ipw + (lane >> seg_log);
-        const bool valid = inst < batch && j < nchunks;
-        uint32_t A[4], B[4], X[4];
-        load_chunk(a + inst * n, n, j, valid, A);
-        load_chunk(b + inst * n, n, j, valid, B);
-        const uint64_t keep = ballot(valid && j + 1 < nchunks);
-        auto add = [&](const uint32_t (&y)[4]) {
-            uint32_t s[4];
-            const uint32_t gen = add_words<4>(X, y, s);
-            const uint64_t G = ballot(gen != 0) & keep, P = ballot(all_ones<4>(s)) & keep;
-            add_carry_words<4>(s, uint32_t(wave_carry(G, P, 0).into >> lane) & 1u);
+    for (uint64_t g = uint64_t(blockIdx.x) * 4 + wave; g * ipw * ROWS < batch; g += uint64_t(gridDim.x) * 4) {
+        const uint64_t inst0 = g * ipw * ROWS + (lane >> seg_log);
+        uint32_t A[ROWS][4], B[ROWS][4], X[ROWS][4];
+        bool valid[ROWS];
+        if (n >= 4) {
+            u32x4 va[ROWS], vb[ROWS];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) X[t] = s[t];
-        };
+            for (int r = 0; r < ROWS; ++r) {
+                const uint64_t at = min(inst0 + r * ipw, batch - 1) * n;
+                va[r] = load_raw<NTL>(a + at, n, j);
+                vb[r] = load_raw<NTL>(b + at, n, j);
+            }
 #pragma unroll
-        for (int t = 0; t < 4; ++t) X[t] = A[t];
-        add(B);
-        add(A);
-        add(B);
-        add(A);
-        add(B);
-        add(A);
-        store_chunk(out + inst * n, n, j, valid, X);
+            for (int r = 0; r < ROWS; ++r) {
+                valid[r] = inst0 + r * ipw < batch && j < nchunks;
+                place_words(va[r], n, j, valid[r], A[r]);
+                place_words(vb[r], n, j, valid[r], B[r]);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                valid[r] = inst0 + r * ipw < batch && j < nchunks;
+                load_short(a + (inst0 + r * ipw) * n, n, valid[r], A[r]);
+                load_short(b + (inst0 + r * ipw) * n, n, valid[r], B[r]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const uint64_t keep = ballot(valid[r] && j + 1 < nchunks);
+            auto add = [&](const uint32_t (&y)[4]) {
+                uint32_t s[4];
+                const uint32_t gen = add_words<4>(X[r], y, s);
+                const uint64_t G = ballot(gen != 0) & keep, P = ballot(all_ones<4>(s)) & keep;
+                add_carry_words<4>(s, uint32_t(wave_carry(G, P, 0).into >> lane) & 1u);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) X[r][t] = s[t];
+            };
+#pragma unroll
+            for (int t = 0; t < 4; ++t) X[r][t] = A[r][t];
+            add(B[r]);
+            add(A[r]);
+            add(B[r]);
+            add(A[r]);
+            add(B[r]);
+            add(A[r]);
+            store_chunk<NTS>(out + (inst0 + r * ipw) * n, n, j, valid[r], X[r]);
+        }
     }
 }
 
@@ -107,7 +152,7 @@ __global__ __launch_bounds__(256) void fused_add6_packed_kernel(const uint32_t *
 // scans its rows, publishes (carry out, all-propagate) in one LDS word,
 // and after one barrier applies the carry from the waves below; the summary
 // words alternate between two arrays so one barrier per addition suffices.
-template <int NW, int R>
+template <int NW, int R, bool NTL, bool NTS>
 __global__ __launch_bounds__(64 * NW) void fused_add6_rows_kernel(const uint32_t *__restrict__ a,
                                                                   const uint32_t *__restrict__ b,
                                                                   uint32_t *__restrict__ out, uint32_t n,
@@ -118,12 +163,19 @@ __global__ __launch_bounds__(64 * NW) void fused_add6_rows_kernel(const uint32_t
     for (uint64_t q = blockIdx.x; q < batch; q += gridDim.x) {
         uint32_t A[R][4], B[R][4], X[R][4];
         uint64_t vmask[R];
+        u32x4 va[R], vb[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint32_t row = w * R + r, c = row * 64 + lane;
+            va[r] = load_raw<NTL>(a + q * n, n, c);
+            vb[r] = load_raw<NTL>(b + q * n, n, c);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t c = (w * R + r) * 64 + lane;
             const bool valid = c < nchunks;
-            load_chunk(a + q * n, n, c, valid, A[r]);
-            load_chunk(b + q * n, n, c, valid, B[r]);
+            place_words(va[r], n, c, valid, A[r]);
+            place_words(vb[r], n, c, valid, B[r]);
             vmask[r] = ballot(valid);
 #pragma unroll
             for (int t = 0; t < 4; ++t) X[r][t] = A[r][t];
@@ -168,7 +220,7 @@ __global__ __launch_bounds__(64 * NW) void fused_add6_rows_kernel(const uint32_t
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint32_t c = (w * R + r) * 64 + lane;
-            store_chunk(out + q * n, n, c, c < nchunks, X[r]);
+            store_chunk<NTS>(out + q * n, n, c, c < nchunks, X[r]);
         }
     }
 }
@@ -355,6 +407,9 @@ size_t packed_lds_bytes(bool poly, uint32_t n, uint32_t seg_log) {
 
 // Persistent grid of resident workgroups (each loops over instances).  One
 // instantiation per kernel, so each keeps its own occupancy record.
+// Grids of up to 64 times the resident workgroups: equal persistent shares
+// finish unevenly (2^27 words of 512 / 1024 / 8192 words 299 / 299 / 294 ->
+// 246 / 256 / 282 us; at 8 times 264 / 266 / 295).
 using FusedKernel = void (*)(const uint32_t *, const uint32_t *, uint32_t *, uint32_t, uint64_t);
 template <FusedKernel kernel>
 hipError_t launch_persistent(uint32_t threads, const uint32_t *a, const uint32_t *b, uint32_t *c, uint32_t n,
@@ -368,7 +423,7 @@ hipError_t launch_persistent(uint32_t threads, const uint32_t *a, const uint32_t
         if (o < 1) o = 1;
         occ.store(o, std::memory_order_relaxed);
     }
-    const uint64_t cap = uint64_t(o) * uint64_t(num_cus > 0 ? num_cus : 1);
+    const uint64_t cap = uint64_t(o) * uint64_t(num_cus > 0 ? num_cus : 1) * 64;
     const uint32_t grid = uint32_t(batch < cap ? batch : cap);
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, a, b, c, n, batch);
     return hipGetLastError();
@@ -398,14 +453,31 @@ hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint3
                         hipStream_t st, int num_cus) {
     if (batch == 0) return hipSuccess;
     if (program == BI_PROG_ADD6) {
+        // Bound by HBM.  Results go past the caches as for products (2^25 words
+        // of 128: 72 -> 57 us), unless short odd instances would write partial
+        // lines (2^27 words of 31: 424 -> 495).  Operands beyond twice the
+        // 256 MiB memory-side cache are read past it too (2^27 words of 128:
+        // 329 -> 285; below that 2^25 words 57 -> 64), in aligned rows (257
+        // words 366 -> 394), and from 768 MiB four rows per wavefront are in
+        // flight (2^27 words 269 -> 244, 2^26 words 132 -> 137).  Operands
+        // beyond the cache also run on finer grids (2^27 words of 255: 340 ->
+        // 280; 2^24 words of one 53 -> 63).
+        const uint64_t words = uint64_t(n) * batch;
+        const bool nts = streamed_results(4 * words) && (n % 4 == 0 || n >= 48);
+        const bool ntl = nts && n % 4 == 0 && 8 * words > (uint64_t(512) << 20);
         const uint32_t nchunks = (n + 3) / 4, rows = (nchunks + 63) / 64;
         if (rows == 1) {
             uint32_t seg_log = 0;
             while ((1u << seg_log) < nchunks) ++seg_log;
-            const uint64_t waves = (batch + (64u >> seg_log) - 1) / (64u >> seg_log);
-            const uint64_t cap = uint64_t(num_cus > 0 ? num_cus : 1) * 32;
+            const uint32_t per_wave = ntl && 8 * words > (uint64_t(768) << 20) ? 4 : 1;
+            const uint64_t ipw = per_wave * (64u >> seg_log), waves = (batch + ipw - 1) / ipw;
+            const uint64_t cap = uint64_t(num_cus > 0 ? num_cus : 1) * (8 * words > (uint64_t(256) << 20) ? 256 : 32);
             const uint32_t grid = uint32_t(std::min((waves + 3) / 4, cap));
-            hipLaunchKernelGGL(fused_add6_packed_kernel, dim3(grid), dim3(256), 0, st, a, b, c, n, batch, seg_log);
+            const auto kernel = per_wave == 4 ? fused_add6_packed_kernel<4, true, true>
+                                : ntl ? fused_add6_packed_kernel<1, true, true>
+                                : nts ? fused_add6_packed_kernel<1, false, true>
+                                      : fused_add6_packed_kernel<1, false, false>;
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, a, b, c, n, batch, seg_log);
             return hipGetLastError();
         }
         // up to 4 rows per lane group: fewer waves per instance, more
@@ -414,7 +486,10 @@ hipError_t launch_fused(int program, const uint32_t *a, const uint32_t *b, uint3
         while (4 * nw < rows) nw *= 2;
         const uint32_t r = (rows + nw - 1) / nw;
 #define BI_ADD6_CASE(W, RR) \
-    if (nw == W && r == RR) return launch_persistent<&fused_add6_rows_kernel<W, RR>>(64 * W, a, b, c, n, batch, st, num_cus);
+    if (nw == W && r == RR)                                                                                     \
+        return ntl   ? launch_persistent<&fused_add6_rows_kernel<W, RR, true, true>>(64 * W, a, b, c, n, batch, st, num_cus)  \
+               : nts ? launch_persistent<&fused_add6_rows_kernel<W, RR, false, true>>(64 * W, a, b, c, n, batch, st, num_cus) \
+                     : launch_persistent<&fused_add6_rows_kernel<W, RR, false, false>>(64 * W, a, b, c, n, batch, st, num_cus);
         BI_ADD6_CASE(1, 2) BI_ADD6_CASE(1, 3) BI_ADD6_CASE(1, 4) BI_ADD6_CASE(2, 3) BI_ADD6_CASE(2, 4)
         BI_ADD6_CASE(4, 3) BI_ADD6_CASE(4, 4) BI_ADD6_CASE(8, 3) BI_ADD6_CASE(8, 4)
 #undef BI_ADD6_CASE

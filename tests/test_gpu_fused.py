@@ -125,3 +125,27 @@ def test_paper_workload(B, ctx, orc, name, bits):
     bad = np.nonzero((got[pick] != exp).any(axis=1))[0]
     assert bad.size == 0, f"{name} at {bits} bits: {bad.size} of {pick.size} checked instances differ, " \
                           f"first {pick[bad[:8]].tolist()}"
+
+
+# ragged last chunks, operands and result one word off a 16-byte boundary, a
+# last row and a last group of rows that are not full; 2^22 words and more are
+# stored past the caches, 2^27 read past them in four rows per wavefront
+@pytest.mark.parametrize("words", [1000, 5 << 20, 1 << 27])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 7, 12, 47, 48, 63, 252, 256, 257, 516, 8191])
+def test_add6_streams(B, ctx, n, words):
+    if words == 1 << 27 and n not in (4, 12, 252, 256, 516):
+        pytest.skip("rows of whole 16-byte chunks are read past the caches")
+    batch = max(1, words // n) + 3
+    off = 0 if words == 1 << 27 else 1
+    rng = np.random.default_rng(n)
+    a = np.frombuffer(rng.bytes(4 * (batch * n + off)), np.uint32).copy()
+    b = np.frombuffer(rng.bytes(4 * (batch * n + off)), np.uint32).copy()
+    A, Bt = G.to_dev(a)[off:].reshape(batch, n), G.to_dev(b)[off:].reshape(batch, n)
+    out = G.empty_dev((batch * n + off,), np.uint32)[off:].reshape(batch, n)
+    B.fused(ctx, PROGRAMS["add6"], A, Bt, out)
+    G.sync()
+    pick = np.unique(np.concatenate([np.arange(min(batch, 300)), np.arange(max(0, batch - 300), batch),
+                                     rng.integers(0, batch, 300)]))
+    got = G.from_dev(out, np.uint32)[pick]
+    exp = O.add6(a[off:].reshape(batch, n)[pick], b[off:].reshape(batch, n)[pick])
+    assert np.nonzero((got != exp).any(axis=1))[0].size == 0
