@@ -26,11 +26,50 @@
 
 namespace bi {
 
-template <int W, int U, bool NT>
+// Instances of n words whose length or address 16 does not divide (TAIL, W =
+// 4): chunks of four words at any word address, the last one ragged.  Every
+// lane loads 16 bytes (chunks that end past the instance its last 16: n >= 4,
+// no branch between the loads of several rows) and moves the words into place;
+// missing words read as all ones in a and zero in b, which passes a carry on
+// as if they were not there.  Lanes past the last chunk read zero.
+typedef u32x4 __attribute__((aligned(4))) u32x4_word;
+
+template <bool NT>
+__device__ __forceinline__ u32x4 load_tail(const uint32_t *p, uint32_t n, uint32_t c) {
+    const u32x4_word *q = reinterpret_cast<const u32x4_word *>(p + min(4 * c, n - 4));
+    return NT ? __builtin_nontemporal_load(q) : *q;
+}
+__device__ __forceinline__ void place_tail(const u32x4 &v, uint32_t n, uint32_t c, bool ok, uint32_t missing,
+                                           uint32_t (&x)[4]) {
+    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    if (n & 3u) {
+        const uint32_t s = 4 * c + 4 > n ? 4 * c + 4 - n : 0u;  // words of the chunk past n
+        if (s & 1u) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; x[3] = missing; }
+        if (s & 2u) { x[0] = x[2]; x[1] = x[3]; x[2] = missing; x[3] = missing; }
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) x[t] = ok ? x[t] : 0u;
+}
+template <bool NT>
+__device__ __forceinline__ void store_tail(uint32_t *p, uint32_t n, uint32_t c, const uint32_t (&x)[4]) {
+    const uint32_t base = 4 * c;
+    if (base + 4 <= n) {
+        const u32x4 v = {x[0], x[1], x[2], x[3]};
+        u32x4_word *q = reinterpret_cast<u32x4_word *>(p + base);
+        if (NT) __builtin_nontemporal_store(v, q); else *q = v;
+    } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (base + t < n) p[base + t] = x[t];
+    }
+}
+
+// (`n`: words per instance, read with TAIL only)
+template <int W, int U, bool NT, bool TAIL>
 __global__ __launch_bounds__(256) void bigadd_packed_kernel(const uint32_t *__restrict__ a,
                                                             const uint32_t *__restrict__ b,
                                                             uint32_t *out, uint8_t *carry,
-                                                            uint32_t m, uint32_t ipr, uint64_t batch) {
+                                                            uint32_t m, uint32_t n, uint32_t ipr, uint64_t batch) {
     const uint32_t lane = lane_id();
     const uint64_t wave = wave_global();
     const uint64_t nwaves = (uint64_t(gridDim.x) * blockDim.x) >> 6;
@@ -43,11 +82,23 @@ __global__ __launch_bounds__(256) void bigadd_packed_kernel(const uint32_t *__re
     for (uint64_t r0 = wave * U; r0 < nrows; r0 += nwaves * U) {
         uint32_t va[U][W], vb[U][W];
         bool ok[U];
+        u32x4 ra[U], rb[U];
+        if constexpr (TAIL) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint64_t off = min((r0 + u) * ipr + slot, batch - 1) * n;
+                ra[u] = load_tail<NT>(a + off, n, pos);
+                rb[u] = load_tail<NT>(b + off, n, pos);
+            }
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint64_t inst = (r0 + u) * ipr + slot;
             ok[u] = in_row && (r0 + u) < nrows && inst < batch;
-            if (ok[u]) {
+            if constexpr (TAIL) {
+                place_tail(ra[u], n, pos, ok[u], ~0u, va[u]);
+                place_tail(rb[u], n, pos, ok[u], 0u, vb[u]);
+            } else if (ok[u]) {
                 const uint64_t off = (inst * m + pos) * W;
                 load_words<W, NT>(a + off, va[u]);
                 load_words<W, NT>(b + off, vb[u]);
@@ -66,7 +117,8 @@ __global__ __launch_bounds__(256) void bigadd_packed_kernel(const uint32_t *__re
                 const uint64_t inst = (r0 + u) * ipr + slot;
                 if (carry && pos == m - 1) carry[inst] = uint8_t(g | (p & cin));
                 add_carry_words<W>(s, cin);
-                store_words<W, NT>(out + (inst * m + pos) * W, s);
+                if constexpr (TAIL) store_tail<NT>(out + inst * n, n, pos, s);
+                else store_words<W, NT>(out + (inst * m + pos) * W, s);
             }
         }
     }
@@ -74,6 +126,44 @@ __global__ __launch_bounds__(256) void bigadd_packed_kernel(const uint32_t *__re
 
 // One wavefront adds one instance of m chunks, least significant row first.
 // Returns (in every lane) the carry out of the instance.
+template <int U>
+__device__ __forceinline__ uint32_t add_instance_tail(const uint32_t *__restrict__ ai,
+                                                      const uint32_t *__restrict__ bi_, uint32_t *oi, uint32_t n,
+                                                      uint32_t lane) {
+    const uint32_t m = (n + 3) / 4, rows = (m + 63) / 64;
+    uint32_t cin_row = 0;
+    for (uint32_t r0 = 0; r0 < rows; r0 += U) {
+        u32x4 ra[U], rb[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t c = (r0 + u) * 64 + lane;
+            if (r0 + u < rows) {  // uniform
+                ra[u] = load_tail<false>(ai, n, c);
+                rb[u] = load_tail<false>(bi_, n, c);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r0 + u < rows) {  // uniform
+                const uint32_t c = (r0 + u) * 64 + lane;
+                const bool ok = c < m;
+                uint32_t va[4], vb[4], s[4];
+                place_tail(ra[u], n, c, ok, ~0u, va);
+                place_tail(rb[u], n, c, ok, 0u, vb);
+                const uint32_t g = add_words<4>(va, vb, s);
+                const WaveCarry wc = wave_carry(ballot(ok && g), ballot(ok && all_ones<4>(s)), cin_row);
+                if (ok) {
+                    add_carry_words<4>(s, uint32_t(wc.into >> lane) & 1u);
+                    store_tail<false>(oi, n, c, s);
+                }
+                const uint32_t valid = m - (r0 + u) * 64;
+                cin_row = valid >= 64 ? wc.out : uint32_t(wc.into >> valid) & 1u;
+            }
+        }
+    }
+    return cin_row;
+}
+
 template <int W, int U, bool NT>
 __device__ __forceinline__ uint32_t add_instance_streamed(const uint32_t *__restrict__ ai,
                                                           const uint32_t *__restrict__ bi_, uint32_t *oi,
@@ -116,7 +206,11 @@ __device__ __forceinline__ uint32_t add_instance_streamed(const uint32_t *__rest
     return cin_row;
 }
 
-// Ragged batch: one wavefront per descriptor, chunks of one limb (W words).
+// Ragged batch: one wavefront per descriptor, chunks of 16 bytes at any word
+// address above 64 limbs (one limb per lane at every size: 5000 instances of
+// 2^8 .. 2^18 bits 41 -> 20 us, 100 of 2^10 .. 2^18 27 -> 12), of one limb, W
+// words, in the one row of shorter ones (100000 of 2^8 .. 2^12 bits: 21 us, 26
+// in 16-byte chunks).
 template <int W, int U>
 __global__ __launch_bounds__(256) void bigadd_ragged_kernel(const uint32_t *__restrict__ a,
                                                             const uint32_t *__restrict__ b,
@@ -127,8 +221,10 @@ __global__ __launch_bounds__(256) void bigadd_ragged_kernel(const uint32_t *__re
     const uint64_t nwaves = (uint64_t(gridDim.x) * blockDim.x) >> 6;
     for (uint64_t i = wave; i < count; i += nwaves) {
         const bi_desc d = desc[i];
-        const uint32_t c = add_instance_streamed<W, U, false>(a + d.a_off * W, b + d.b_off * W, out + d.out_off * W,
-                                                       d.n_limbs, lane);
+        const uint32_t *ai = a + d.a_off * W, *bi_ = b + d.b_off * W;
+        uint32_t *oi = out + d.out_off * W;
+        const uint32_t c = d.n_limbs > 64 ? add_instance_tail<U>(ai, bi_, oi, d.n_limbs * W, lane)
+                                          : add_instance_streamed<W, 1, false>(ai, bi_, oi, d.n_limbs, lane);
         if (carry && lane == 0) carry[i] = uint8_t(c);
     }
 }
@@ -140,11 +236,11 @@ __global__ __launch_bounds__(256) void bigadd_ragged_kernel(const uint32_t *__re
 // summaries through LDS, and then apply their true carry-in.  This is the
 // thread -> wave -> block hierarchy of the paper's block scan, with one
 // ballot-adder step per level.
-template <int W, int U, int NW, bool NT>
+template <int W, int U, int NW, bool NT, bool TAIL>
 __global__ __launch_bounds__(64 * NW) void bigadd_coop_kernel(const uint32_t *__restrict__ a,
                                                               const uint32_t *__restrict__ b,
                                                               uint32_t *out, uint8_t *carry, uint32_t m,
-                                                              uint64_t batch) {
+                                                              uint32_t n, uint64_t batch) {
     __shared__ uint32_t summ[NW];
     const uint32_t lane = lane_id();
     const uint32_t wave = wave_in_block();
@@ -152,7 +248,7 @@ __global__ __launch_bounds__(64 * NW) void bigadd_coop_kernel(const uint32_t *__
     const uint32_t tiles = (rows + NW * U - 1) / (NW * U);
 
     for (uint64_t inst = blockIdx.x; inst < batch; inst += gridDim.x) {
-        const uint64_t off = inst * m * W;
+        const uint64_t off = TAIL ? inst * n : inst * m * W;
         const uint32_t *ai = a + off;
         const uint32_t *bi_ = b + off;
         uint32_t *oi = out + off;
@@ -162,13 +258,24 @@ __global__ __launch_bounds__(64 * NW) void bigadd_coop_kernel(const uint32_t *__
             uint32_t s[U][W];
             uint64_t G[U], P[U];
             uint32_t gl[U], pl[U];
+            u32x4 ra[U], rb[U];
+            if constexpr (TAIL) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    ra[u] = load_tail<NT>(ai, n, (r0 + u) * 64 + lane);
+                    rb[u] = load_tail<NT>(bi_, n, (r0 + u) * 64 + lane);
+                }
+            }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const uint32_t c = (r0 + u) * 64 + lane;
                 uint32_t va[W], vb[W];
 #pragma unroll
                 for (int w = 0; w < W; ++w) { va[w] = 0; vb[w] = 0; }
-                if (c < m) {
+                if constexpr (TAIL) {
+                    place_tail(ra[u], n, c, c < m, ~0u, va);
+                    place_tail(rb[u], n, c, c < m, 0u, vb);
+                } else if (c < m) {
                     load_words<W, NT>(ai + uint64_t(c) * W, va);
                     load_words<W, NT>(bi_ + uint64_t(c) * W, vb);
                 }
@@ -207,7 +314,11 @@ __global__ __launch_bounds__(64 * NW) void bigadd_coop_kernel(const uint32_t *__
                     const WaveCarry wc = wave_carry(G[u], P[u], cin);
                     const uint32_t ci = uint32_t(wc.into >> lane) & 1u;
                     add_carry_words<W>(s[u], ci);
-                    if (c < m) store_words<W, NT>(oi + uint64_t(c) * W, s[u]);
+                    if constexpr (TAIL) {
+                        if (c < m) store_tail<NT>(oi, n, c, s[u]);
+                    } else {
+                        if (c < m) store_words<W, NT>(oi + uint64_t(c) * W, s[u]);
+                    }
                     cin = valid >= 64 ? wc.out : uint32_t(wc.into >> valid) & 1u;
                 }
             }
@@ -221,17 +332,29 @@ __global__ __launch_bounds__(64 * NW) void bigadd_coop_kernel(const uint32_t *__
 // Barrier-free schedule for instances of RPI rows (2 to 8): one wavefront
 // loads U whole instances (U * RPI rows) before consuming any, then chains
 // the scalar carry through each instance's rows.
-template <int W, int U, int RPI, bool NT>
+template <int W, int U, int RPI, bool NT, bool TAIL>
 __global__ __launch_bounds__(256) void bigadd_multi_kernel(const uint32_t *__restrict__ a,
                                                            const uint32_t *__restrict__ b,
                                                            uint32_t *out, uint8_t *carry, uint32_t m,
-                                                           uint64_t batch) {
+                                                           uint32_t n, uint64_t batch) {
     const uint32_t lane = lane_id();
     const uint64_t wave = wave_global();
     const uint64_t nwaves = (uint64_t(gridDim.x) * blockDim.x) >> 6;
     for (uint64_t i0 = wave * U; i0 < batch; i0 += nwaves * U) {
         uint32_t s[U][RPI][W];
         uint32_t gl[U][RPI], pl[U][RPI];
+        u32x4 ra[U][RPI], rb[U][RPI];
+        if constexpr (TAIL) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint64_t off = min(i0 + u, batch - 1) * n;
+#pragma unroll
+                for (int r = 0; r < RPI; ++r) {
+                    ra[u][r] = load_tail<NT>(a + off, n, r * 64 + lane);
+                    rb[u][r] = load_tail<NT>(b + off, n, r * 64 + lane);
+                }
+            }
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
 #pragma unroll
@@ -241,7 +364,10 @@ __global__ __launch_bounds__(256) void bigadd_multi_kernel(const uint32_t *__res
 #pragma unroll
                 for (int w = 0; w < W; ++w) { va[w] = 0; vb[w] = 0; }
                 const bool ok = (i0 + u < batch) && c < m;
-                if (ok) {
+                if constexpr (TAIL) {
+                    place_tail(ra[u][r], n, c, ok, ~0u, va);
+                    place_tail(rb[u][r], n, c, ok, 0u, vb);
+                } else if (ok) {
                     const uint64_t off = ((i0 + u) * m + c) * W;
                     load_words<W, NT>(a + off, va);
                     load_words<W, NT>(b + off, vb);
@@ -262,7 +388,11 @@ __global__ __launch_bounds__(256) void bigadd_multi_kernel(const uint32_t *__res
                 const WaveCarry wc = wave_carry(G, P, cin);
                 const uint32_t ci = uint32_t(wc.into >> lane) & 1u;
                 add_carry_words<W>(s[u][r], ci);
-                if (c < m) store_words<W, NT>(out + ((i0 + u) * m + c) * W, s[u][r]);
+                if constexpr (TAIL) {
+                    if (c < m) store_tail<NT>(out + (i0 + u) * n, n, c, s[u][r]);
+                } else {
+                    if (c < m) store_words<W, NT>(out + ((i0 + u) * m + c) * W, s[u][r]);
+                }
                 const uint32_t valid = min(m - r * 64, 64u);
                 cin = valid >= 64 ? wc.out : uint32_t(wc.into >> valid) & 1u;
             }
@@ -280,17 +410,17 @@ static int pick_chunk_bytes(uint64_t inst_bytes, const void *a, const void *b, c
     return 4;
 }
 
-template <int W, int U, bool NT>
+template <int W, int U, bool NT, bool TAIL>
 static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, uint8_t *carry, uint64_t m,
-                            uint64_t batch, hipStream_t st, uint64_t max_waves, bool multi) {
+                            uint32_t n, uint64_t batch, hipStream_t st, uint64_t max_waves, bool multi) {
     if (m <= 64) {
         const uint32_t ipr = uint32_t(64 / m);
         const uint64_t nrows = (batch + ipr - 1) / ipr;
         uint64_t waves = (nrows + U - 1) / U;
         if (waves > max_waves) waves = max_waves;
         const uint64_t blocks = (waves + 3) / 4;
-        hipLaunchKernelGGL((bigadd_packed_kernel<W, U, NT>), dim3(uint32_t(blocks)), dim3(256), 0, st, a, b, o, carry,
-                           uint32_t(m), ipr, batch);
+        hipLaunchKernelGGL((bigadd_packed_kernel<W, U, NT, TAIL>), dim3(uint32_t(blocks)), dim3(256), 0, st, a, b, o, carry,
+                           uint32_t(m), n, ipr, batch);
     } else if (multi && m <= 8 * 64) {
         // Up to 8 rows: one wave per instance, `U` instances in flight.
         const uint64_t rows = (m + 63) / 64;
@@ -298,13 +428,13 @@ static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, u
         if (waves > max_waves) waves = max_waves;
         const dim3 g{uint32_t((waves + 3) / 4), 1, 1};
         if (rows <= 2)
-            hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 2 ? U / 2 : 1), 2, NT>), g, dim3(256), 0, st, a, b, o,
-                               carry, uint32_t(m), batch);
+            hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 2 ? U / 2 : 1), 2, NT, TAIL>), g, dim3(256), 0, st, a, b, o,
+                               carry, uint32_t(m), n, batch);
         else if (rows <= 4)
-            hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 4 ? U / 4 : 1), 4, NT>), g, dim3(256), 0, st, a, b, o,
-                               carry, uint32_t(m), batch);
+            hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 4 ? U / 4 : 1), 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o,
+                               carry, uint32_t(m), n, batch);
         else
-            hipLaunchKernelGGL((bigadd_multi_kernel<W, 1, 8, NT>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m),
+            hipLaunchKernelGGL((bigadd_multi_kernel<W, 1, 8, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), n,
                                batch);
     } else {
         // One workgroup per instance: NW waves x UC rows cover the instance
@@ -315,33 +445,33 @@ static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, u
         if (wgs > cap) wgs = cap;
         const dim3 g{uint32_t(wgs), 1, 1};
         if (rows <= 2) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 2, NT>), g, dim3(128), 0, st, a, b, o, carry, uint32_t(m), batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 2, NT, TAIL>), g, dim3(128), 0, st, a, b, o, carry, uint32_t(m), n, batch);
         } else if (rows <= 4) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 4, NT>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), n, batch);
         } else if (rows <= 8) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 4, NT>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), n, batch);
         } else if (rows <= 16) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 8, NT>), g, dim3(512), 0, st, a, b, o, carry, uint32_t(m), batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 8, NT, TAIL>), g, dim3(512), 0, st, a, b, o, carry, uint32_t(m), n, batch);
         } else {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 4, 8, NT>), g, dim3(512), 0, st, a, b, o, carry, uint32_t(m), batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 4, 8, NT, TAIL>), g, dim3(512), 0, st, a, b, o, carry, uint32_t(m), n, batch);
         }
     }
     return hipGetLastError();
 }
 
-template <int W>
-static hipError_t launch_w(const uint32_t *a, const uint32_t *b, uint32_t *o, uint8_t *carry, uint64_t m,
+template <int W, bool TAIL>
+static hipError_t launch_w(const uint32_t *a, const uint32_t *b, uint32_t *o, uint8_t *carry, uint64_t m, uint32_t n,
                            uint64_t batch, hipStream_t st, const AddTune &t) {
     const uint64_t mw = t.max_waves;
     const bool mu = (m <= 8 * 64) && ((m <= 2 * 64) ? t.multi2 : (m <= 4 * 64) ? t.multi4 : t.multi8);
     if (t.nt) {
-        if (t.rows == 2) return launch_wu<W, 2, true>(a, b, o, carry, m, batch, st, mw, mu);
-        if (t.rows == 8) return launch_wu<W, 8, true>(a, b, o, carry, m, batch, st, mw, mu);
-        return launch_wu<W, 4, true>(a, b, o, carry, m, batch, st, mw, mu);
+        if (t.rows == 2) return launch_wu<W, 2, true, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
+        if (t.rows == 8) return launch_wu<W, 8, true, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
+        return launch_wu<W, 4, true, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
     }
-    if (t.rows == 2) return launch_wu<W, 2, false>(a, b, o, carry, m, batch, st, mw, mu);
-    if (t.rows == 8) return launch_wu<W, 8, false>(a, b, o, carry, m, batch, st, mw, mu);
-    return launch_wu<W, 4, false>(a, b, o, carry, m, batch, st, mw, mu);
+    if (t.rows == 2) return launch_wu<W, 2, false, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
+    if (t.rows == 8) return launch_wu<W, 8, false, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
+    return launch_wu<W, 4, false, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
 }
 
 hipError_t launch_bigadd_ragged(const void *a, const void *b, void *out, uint8_t *carry, const bi_desc *desc,
@@ -364,14 +494,19 @@ hipError_t launch_bigadd(const void *a, const void *b, void *out, uint8_t *carry
     if (batch == 0) return hipSuccess;
     const int cb = pick_chunk_bytes(inst_bytes, a, b, out);
     const uint64_t m = inst_bytes / cb;
+    const uint32_t n = uint32_t(inst_bytes / 4);
     auto A = static_cast<const uint32_t *>(a);
     auto B = static_cast<const uint32_t *>(b);
     auto O = static_cast<uint32_t *>(out);
-    switch (cb) {
-        case 16: return launch_w<4>(A, B, O, carry, m, batch, st, t);
-        case 8: return launch_w<2>(A, B, O, carry, m, batch, st, t);
-        default: return launch_w<1>(A, B, O, carry, m, batch, st, t);
-    }
+    if (cb == 16) return launch_w<4, false>(A, B, O, carry, m, n, batch, st, t);
+    // Word-aligned instances of more than one narrow row: ragged 16-byte chunks
+    // (2^27 words of 65 / 257 / 577 / 1001 / 8191 words 540 / 470 / 636 / 423 /
+    // 321 -> 335 / 320 / 309 / 314 / 273 us).  Not 129 .. 192 words, whose 33 ..
+    // 48 chunks leave a row's other lanes idle (129 words: 336 -> 369), nor
+    // 8-byte chunks (130 / 1022 words: 355 / 267 -> 377 / 306).
+    if (cb == 4 && m > 64 && !(n > 128 && n <= 192)) return launch_w<4, true>(A, B, O, carry, (uint64_t(n) + 3) / 4, n, batch, st, t);
+    return cb == 8 ? launch_w<2, false>(A, B, O, carry, m, n, batch, st, t)
+                   : launch_w<1, false>(A, B, O, carry, m, n, batch, st, t);
 }
 
 }  // namespace bi

@@ -184,3 +184,52 @@ def test_tuning_variants(B, orc, tune, monkeypatch):
             check(orc, a, b, got, carry)
     finally:
         c.close()
+
+
+# operands and result one word off a 16-byte boundary, so instances of more
+# than 64 words take ragged 16-byte chunks (all but 129 .. 192 words)
+@pytest.mark.parametrize("n", [64, 65, 66, 67, 68, 127, 128, 129, 192, 193, 255, 256, 257, 258, 259, 513, 1021, 1025, 2047,
+                               2049, 4097, 8189, 8190, 8191, 8192])
+def test_word_aligned(B, ctx, orc, n):
+    batch = 37
+    rng = np.random.default_rng(n)
+    a, b = (rng.integers(0, 2**32, (batch, n), dtype=np.uint64).astype(np.uint32) for _ in range(2))
+    a[:4] = 0xFFFFFFFF
+    b[0] = 0xFFFFFFFF
+    b[1] = b[2] = 0
+    b[1, 0] = 1          # the carry runs out of the top
+    b[3, 1:], b[3, 0] = 0, 1
+    a[3, n - 1] = 7      # the carry stops in the last word
+    exp, cexp = orc.add(a, b)
+    pad = lambda x: G.to_dev(np.concatenate([[0], x.ravel()]).astype(np.uint32))[1:].reshape(batch, n)
+    A, Bt = pad(a), pad(b)
+    for out in (G.empty_dev((batch * n + 1,), np.uint32)[1:].reshape(batch, n), A):  # the second in place
+        carry = G.zeros_u8(batch)
+        B.bigadd(ctx, A, Bt, out, carry)
+        G.sync()
+        assert (G.from_dev(out, np.uint32) == exp).all()
+        assert (carry.cpu().numpy() == cexp).all()
+
+
+@pytest.mark.parametrize("limb_bits", [32, 64])
+def test_ragged_chunks(B, ctx, orc, limb_bits):
+    """Ragged sizes around the change from limbs to 16-byte chunks, at every
+    word alignment, carries out of the top."""
+    sizes = np.array([1, 2, 63, 64, 65, 66, 67, 68, 127, 128, 129, 255, 256, 257, 511, 1021, 2047, 4095, 30, 65], np.uint32)
+    dt = np.uint32 if limb_bits == 32 else np.uint64
+    rng = np.random.default_rng(limb_bits)
+    off = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.uint64)
+    tot = int(sizes.sum())
+    a, b = (rng.integers(0, np.iinfo(dt).max, tot, dtype=dt, endpoint=True) for _ in range(2))
+    for i in range(0, len(sizes), 2):
+        s = slice(int(off[i]), int(off[i] + sizes[i]))
+        a[s], b[s] = np.iinfo(dt).max, 0
+        b[s.start] = 1
+    out, carry = G.empty_dev(tot, dt), G.zeros_u8(len(sizes))
+    B.bigadd_v(ctx, G.to_dev(a), G.to_dev(b), out, carry, G.desc_dev(off, off, off, sizes), len(sizes), limb_bits)
+    G.sync()
+    got, gc = G.from_dev(out, dt), carry.cpu().numpy()
+    for i in range(len(sizes)):
+        s = slice(int(off[i]), int(off[i] + sizes[i]))
+        e, c = orc.add(a[None, s], b[None, s])
+        assert (got[s] == e[0]).all() and gc[i] == c[0], (i, sizes[i])
