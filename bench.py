@@ -144,14 +144,14 @@ def add_kernel_name(n_limbs, limb_bits):
     chunks; mirrors the size classes of the launcher in csrc/bigadd.hip)."""
     m = n_limbs * limb_bits // 128
     if m <= 64:
-        return "bi::bigadd_packed_kernel<4, 4, true>"
+        return "bi::bigadd_packed_kernel<4, 4, true, false>"
     rows = (m + 63) // 64
     if rows <= 2:
-        return "bi::bigadd_multi_kernel<4, 2, 2, true>"
+        return "bi::bigadd_multi_kernel<4, 2, 2, true, false>"
     if rows <= 4:
-        return "bi::bigadd_multi_kernel<4, 1, 4, true>"
+        return "bi::bigadd_multi_kernel<4, 1, 4, true, false>"
     u, nw = (1, 2) if rows <= 2 else (1, 4) if rows <= 4 else (2, 4) if rows <= 8 else (2, 8) if rows <= 16 else (4, 8)
-    return f"bi::bigadd_coop_kernel<4, {u}, {nw}, true>"
+    return f"bi::bigadd_coop_kernel<4, {u}, {nw}, true, false>"
 
 
 def bench_add(args):
