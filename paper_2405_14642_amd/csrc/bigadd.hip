@@ -64,12 +64,13 @@ __device__ __forceinline__ void store_tail(uint32_t *p, uint32_t n, uint32_t c, 
     }
 }
 
-// (`n`: words per instance, read with TAIL only)
+// `len`: words (TAIL) or chunks per instance.
 template <int W, int U, bool NT, bool TAIL>
 __global__ __launch_bounds__(256) void bigadd_packed_kernel(const uint32_t *__restrict__ a,
                                                             const uint32_t *__restrict__ b,
                                                             uint32_t *out, uint8_t *carry,
-                                                            uint32_t m, uint32_t n, uint32_t ipr, uint64_t batch) {
+                                                            uint32_t len, uint32_t ipr, uint64_t batch) {
+    const uint32_t n = len, m = TAIL ? (len + 3) / 4 : len;
     const uint32_t lane = lane_id();
     const uint64_t wave = wave_global();
     const uint64_t nwaves = (uint64_t(gridDim.x) * blockDim.x) >> 6;
@@ -239,8 +240,9 @@ __global__ __launch_bounds__(256) void bigadd_ragged_kernel(const uint32_t *__re
 template <int W, int U, int NW, bool NT, bool TAIL>
 __global__ __launch_bounds__(64 * NW) void bigadd_coop_kernel(const uint32_t *__restrict__ a,
                                                               const uint32_t *__restrict__ b,
-                                                              uint32_t *out, uint8_t *carry, uint32_t m,
-                                                              uint32_t n, uint64_t batch) {
+                                                              uint32_t *out, uint8_t *carry, uint32_t len,
+                                                              uint64_t batch) {
+    const uint32_t n = len, m = TAIL ? (len + 3) / 4 : len;
     __shared__ uint32_t summ[NW];
     const uint32_t lane = lane_id();
     const uint32_t wave = wave_in_block();
@@ -335,8 +337,9 @@ __global__ __launch_bounds__(64 * NW) void bigadd_coop_kernel(const uint32_t *__
 template <int W, int U, int RPI, bool NT, bool TAIL>
 __global__ __launch_bounds__(256) void bigadd_multi_kernel(const uint32_t *__restrict__ a,
                                                            const uint32_t *__restrict__ b,
-                                                           uint32_t *out, uint8_t *carry, uint32_t m,
-                                                           uint32_t n, uint64_t batch) {
+                                                           uint32_t *out, uint8_t *carry, uint32_t len,
+                                                           uint64_t batch) {
+    const uint32_t n = len, m = TAIL ? (len + 3) / 4 : len;
     const uint32_t lane = lane_id();
     const uint64_t wave = wave_global();
     const uint64_t nwaves = (uint64_t(gridDim.x) * blockDim.x) >> 6;
@@ -413,6 +416,7 @@ static int pick_chunk_bytes(uint64_t inst_bytes, const void *a, const void *b, c
 template <int W, int U, bool NT, bool TAIL>
 static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, uint8_t *carry, uint64_t m,
                             uint32_t n, uint64_t batch, hipStream_t st, uint64_t max_waves, bool multi) {
+    const uint32_t len = TAIL ? n : uint32_t(m);
     if (m <= 64) {
         const uint32_t ipr = uint32_t(64 / m);
         const uint64_t nrows = (batch + ipr - 1) / ipr;
@@ -420,7 +424,7 @@ static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, u
         if (waves > max_waves) waves = max_waves;
         const uint64_t blocks = (waves + 3) / 4;
         hipLaunchKernelGGL((bigadd_packed_kernel<W, U, NT, TAIL>), dim3(uint32_t(blocks)), dim3(256), 0, st, a, b, o, carry,
-                           uint32_t(m), n, ipr, batch);
+                           len, ipr, batch);
     } else if (multi && m <= 8 * 64) {
         // Up to 8 rows: one wave per instance, `U` instances in flight.
         const uint64_t rows = (m + 63) / 64;
@@ -429,13 +433,12 @@ static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, u
         const dim3 g{uint32_t((waves + 3) / 4), 1, 1};
         if (rows <= 2)
             hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 2 ? U / 2 : 1), 2, NT, TAIL>), g, dim3(256), 0, st, a, b, o,
-                               carry, uint32_t(m), n, batch);
+                               carry, len, batch);
         else if (rows <= 4)
             hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 4 ? U / 4 : 1), 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o,
-                               carry, uint32_t(m), n, batch);
+                               carry, len, batch);
         else
-            hipLaunchKernelGGL((bigadd_multi_kernel<W, 1, 8, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), n,
-                               batch);
+            hipLaunchKernelGGL((bigadd_multi_kernel<W, 1, 8, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, len, batch);
     } else {
         // One workgroup per instance: NW waves x UC rows cover the instance
         // in one tile when it has at most 32 rows.
@@ -445,15 +448,15 @@ static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, u
         if (wgs > cap) wgs = cap;
         const dim3 g{uint32_t(wgs), 1, 1};
         if (rows <= 2) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 2, NT, TAIL>), g, dim3(128), 0, st, a, b, o, carry, uint32_t(m), n, batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 2, NT, TAIL>), g, dim3(128), 0, st, a, b, o, carry, len, batch);
         } else if (rows <= 4) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), n, batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 1, 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, len, batch);
         } else if (rows <= 8) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, uint32_t(m), n, batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, len, batch);
         } else if (rows <= 16) {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 8, NT, TAIL>), g, dim3(512), 0, st, a, b, o, carry, uint32_t(m), n, batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 2, 8, NT, TAIL>), g, dim3(512), 0, st, a, b, o, carry, len, batch);
         } else {
-            hipLaunchKernelGGL((bigadd_coop_kernel<W, 4, 8, NT, TAIL>), g, dim3(512), 0, st, a, b, o, carry, uint32_t(m), n, batch);
+            hipLaunchKernelGGL((bigadd_coop_kernel<W, 4, 8, NT, TAIL>), g, dim3(512), 0, st, a, b, o, carry, len, batch);
         }
     }
     return hipGetLastError();
