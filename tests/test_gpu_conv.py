@@ -141,3 +141,23 @@ def test_packed_full(B, ctx, orc, n, off):
         B.bigmul(ctx, padded(a, off), padded(b, off), out, algo=VALU)
         G.sync()
         assert differing(G.from_dev(out, np.uint32), orc.mul(a, b)) == [], (n, off, batch)
+
+
+# one workgroup bins up to 4096 descriptors, a grid of them more; a class may
+# be absent, and the classes up to 128 words share one launch
+@pytest.mark.parametrize("algo", [0, MFMA])
+@pytest.mark.parametrize("sizes", [[5], [30, 100], [3, 20, 50, 120, 300]], ids=["one", "two", "five"])
+@pytest.mark.parametrize("count", [1, 3, 1025, 4096, 4097])
+def test_ragged_counts(B, ctx, orc, count, sizes, algo):
+    n = np.random.default_rng(count).choice(sizes, count)
+    off = np.concatenate([[0], np.cumsum(n)[:-1]])
+    rng = np.random.default_rng(5)
+    a, b = (rng.integers(0, 2**32, int(n.sum()), dtype=np.uint32) for _ in range(2))
+    out = G.empty_dev((2 * a.size,), np.uint32)
+    B.bigmul_v(ctx, G.to_dev(a), G.to_dev(b), out, G.desc_dev(off, off, 2 * off, n), len(n), 32, algo=algo)
+    G.sync()
+    got = G.from_dev(out, np.uint32)
+    for k in sizes:
+        at = off[n == k][:, None]
+        rows, cols = at + np.arange(k), 2 * at + np.arange(2 * k)
+        assert (got[cols] == orc.mul(a[rows], b[rows])).all() if at.size else True, k
