@@ -262,11 +262,13 @@ struct Wg {
         for (int i = 0; i < RW; ++i)
             if (stored(i)) *reinterpret_cast<uint4 *>(lds + lo.b + 16 * (kBPad + chunk(i))) = reversed(d[i]);
     }
-    // The top digits where no lane holds their chunk.
+    // The top digits where no lane holds their chunk.  ST: for every product,
+    // since its steps read the chunk whatever its size and a longer product may
+    // have left a digit there (t is 0 for a product with fewer chunks than lanes).
     __device__ __forceinline__ void put_top(const uint32_t (&t)[2]) const {
-        if (nch == LANES && threadIdx.x == 0) {
-            *reinterpret_cast<uint4 *>(lds + kAPad + 16 * nch) = make_uint4(t[0], 0, 0, 0);
-            *reinterpret_cast<uint4 *>(lds + lo.b + 16 * (kBPad + nch)) = make_uint4(0, 0, 0, t[1] << 24);
+        if ((ST ? LANES == CAP : nch == LANES) && threadIdx.x == 0) {
+            *reinterpret_cast<uint4 *>(lds + kAPad + 16 * LANES) = make_uint4(t[0], 0, 0, 0);
+            *reinterpret_cast<uint4 *>(lds + lo.b + 16 * (kBPad + LANES)) = make_uint4(0, 0, 0, t[1] << 24);
         }
     }
 

@@ -161,3 +161,55 @@ def test_ragged_counts(B, ctx, orc, count, sizes, algo):
         at = off[n == k][:, None]
         rows, cols = at + np.arange(k), 2 * at + np.arange(2 * k)
         assert (got[cols] == orc.mul(a[rows], b[rows])).all() if at.size else True, k
+
+
+def run_looping(B, ctx, orc, sizes, count, algo):
+    """`count` products of shuffled sizes in one list: half of them of the
+    first (largest) size, half of those all ones.  Descriptors share 24 operand
+    pairs per size; every word of every result is compared, on the device."""
+    import torch
+    rng = np.random.default_rng(count)
+    pairs, nmax = 24, max(sizes)
+    a, b = (rng.integers(0, 2**32, (len(sizes) * pairs, nmax), dtype=np.uint32) for _ in range(2))
+    a[:pairs // 2] = 0xFFFFFFFF
+    b[:pairs // 2] = 0xFFFFFFFF
+    exp = np.zeros((len(a), 2 * nmax), np.uint32)
+    for i, n in enumerate(sizes):
+        s = slice(i * pairs, (i + 1) * pairs)
+        exp[s, :2 * n] = orc.mul(np.ascontiguousarray(a[s, :n]), np.ascontiguousarray(b[s, :n]))
+    which = np.where(rng.random(count) < 0.5, 0, rng.integers(0, len(sizes), count))
+    pair = which * pairs + rng.integers(0, pairs, count)
+    out = torch.zeros((count, 2 * nmax), dtype=torch.int32, device="cuda")
+    d = G.desc_dev(pair * nmax, pair * nmax, np.arange(count) * 2 * nmax, np.asarray(sizes)[which])
+    B.bigmul_v(ctx, G.to_dev(a), G.to_dev(b), out, d, count, 32, algo=algo)
+    G.sync()
+    e, p = G.to_dev(exp), torch.from_numpy(pair).cuda()
+    bad = torch.cat([(out[i:i + 4096] != e[p[i:i + 4096]]).any(dim=1) for i in range(0, count, 4096)])
+    at = bad.nonzero().flatten().cpu().numpy()
+    assert at.size == 0, f"{at.size} of {count} differ, of {np.unique(np.asarray(sizes)[which[at]]).tolist()} words"
+
+
+# at least twice as many products as the waves or straight-line workgroups of
+# any grid (4 * 256 per class up to 128 words, 8 times the resident ones above),
+# so that each meets longer and shorter ones in turn
+@pytest.mark.parametrize("sizes,count", [((16, 1, 13), 40000), ((32, 29, 17), 40000), ((64, 61, 33), 20000),
+                                         ((128, 125, 65), 10000), ((256, 253, 200, 129), 70000),
+                                         ((512, 509, 300, 257), 35000), ((1024, 1021, 600, 513), 18000)],
+                         ids=lambda v: str(v[0]) if isinstance(v, tuple) else "")
+def test_ragged_looping(B, ctx, orc, sizes, count):
+    run_looping(B, ctx, orc, sizes, count, MFMA)
+
+
+KARATSUBA = 5
+
+
+# 81, 27 and 9 base products per instance, of sizes that follow the instance's
+@pytest.mark.parametrize("sizes,base,count", [((8192, 8189, 6000, 4097), 512, 420), ((8192, 8189, 6000, 4097), 1024, 640),
+                                              ((4096, 4093, 3000, 2049), 1024, 1900)])
+def test_ragged_karatsuba_looping(B, orc, sizes, base, count):
+    c = B.Context(0)
+    try:
+        B.tune_set_kara(c, [base] * B.NUM_CLASSES)
+        run_looping(B, c, orc, sizes, count, KARATSUBA)
+    finally:
+        c.close()
