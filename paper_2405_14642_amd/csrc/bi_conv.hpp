@@ -34,6 +34,7 @@
 
 #include "bi_common.hpp"
 #include "bi_internal.hpp"
+#include "conv_layout.hpp"
 
 namespace bi {
 namespace conv {
@@ -85,12 +86,11 @@ __device__ __forceinline__ uint4 reversed(const uint32_t (&d)[4]) {
                       __builtin_bswap32(d[0]));
 }
 
-// Operand addresses of a lane, relative to an area of a (kAPad zero bytes
-// before digit 0) and to group 0 of an area of b.
-constexpr uint32_t kAPad = 64;
-// bytes an area of a needs so that step u <= umax stays inside it
+// Bytes an area of a needs so that step u <= umax stays inside it.
 __host__ __device__ constexpr uint32_t a_bytes(uint32_t umax) { return (64 * umax + 84 + 15) & ~15u; }
 
+// Operand addresses of a lane, relative to an area of a (kAPad zero bytes
+// before digit 0) and to group 0 of an area of b.
 struct LaneAddr {
     uint32_t a, sh, b;
 };

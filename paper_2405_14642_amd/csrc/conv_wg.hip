@@ -39,22 +39,6 @@ namespace {
 
 using namespace conv;
 
-constexpr uint32_t kATail = 7;   // 16-byte pieces after a's digits (steps read up to 83 bytes past them)
-constexpr uint32_t kBPad = 32;   // zero groups below group 0 of b: B operand -2 at kappa 0, -1 above
-constexpr uint32_t kBTail = 35;  // groups from the top digit's on: B operand J + 1
-
-// Byte offsets of the dynamic LDS block of products of nch chunks.
-struct WgLayout {
-    uint32_t b, sum, total;
-};
-__host__ __device__ inline WgLayout wg_layout(uint32_t nch) {
-    WgLayout l;
-    l.b = kAPad + 16 * (nch + kATail);              // a: digits, the top digit, zeros
-    l.sum = l.b + 16 * (kBPad + nch + kBTail);      // b: groups, the top digit, zeros
-    l.total = l.sum + 4 * 4 * 64;                // recode, boundary and carry words
-    return l;
-}
-
 // Order of the units over the waves: cost grows with the unit (low products)
 // or peaks in the middle (full ones), and waves w, w + 4, w + 8, .. share a
 // SIMD.
@@ -185,7 +169,7 @@ struct Wg {
     WgLayout lo;
     LaneAddr la;
 
-    __device__ __forceinline__ uint32_t *sums() const { return reinterpret_cast<uint32_t *>(lds + lo.sum); }
+    __device__ __forceinline__ uint32_t *sums() const { return reinterpret_cast<uint32_t *>(lds + wg_layout(CAP, CAP).sum); }
     __device__ __forceinline__ uint32_t chunk(int i) const { return 64 * (pw * RW + uint32_t(i)) + lane; }
     // full products: units u and u + NU / 2 of a wave, whose costs add up to
     // the same for every wave
@@ -225,11 +209,11 @@ struct Wg {
         }
         uint32_t cin[2] = {0, 0};
         if constexpr (NW > 1) {
-            uint32_t *s = sums();
-            if (lane < 2) s[32 * lane + pw] = lane == 0 ? out[0] | (all[0] << 1) : out[1] | (all[1] << 1);
+            uint32_t *s = sums() + kRecodeWords;
+            if (lane < 2) s[lane * kRecodeB + pw] = lane == 0 ? out[0] | (all[0] << 1) : out[1] | (all[1] << 1);
             __syncthreads();
             cin[0] = carry_into(s, NW, pw, &t[0]);
-            cin[1] = carry_into(s + 32, NW, pw, &t[1]);
+            cin[1] = carry_into(s + kRecodeB, NW, pw, &t[1]);
         } else {
             t[0] = out[0];
             t[1] = out[1];
@@ -288,7 +272,7 @@ struct Wg {
         const int32_t gd = LOW ? int32_t(nch) - 1 : int32_t(nch);
         const int32_t U = (16 * int32_t(nch) + (LOW ? 62 : 63)) >> 6;
         const int32_t tiles = LOW ? int32_t(nch + 15) >> 4 : int32_t(nch + 7) >> 3;
-        uint32_t *bnd = sums() + 64, *cs = sums() + 128;
+        uint32_t *bnd = sums() + kBoundaryWords, *cs = sums() + kCarryWords;
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             v4i acc[T] = {};
@@ -374,7 +358,7 @@ __global__ __launch_bounds__(64 * NW, T >= 16 || (T > 8 && MODE == kPoly) ? 2 : 
         w.pw = wave_role<NW, LOW>(wave, inst);
         w.n = in.n;
         w.nch = (in.n + 3) / 4;
-        w.lo = wg_layout(ST ? W::CAP : w.nch);
+        w.lo = wg_layout(ST ? W::CAP : w.nch, W::CAP);
         uint32_t t[2];
         uint32_t b[RW][4];  // Poly: the words of b
         if constexpr (MODE == kPoly) {
@@ -458,21 +442,21 @@ __global__ __launch_bounds__(64 * NW, T >= 16 || (T > 8 && MODE == kPoly) ? 2 : 
 template <int NW, int UPW, int MODE, int T, bool ST, class Src>
 static hipError_t launch_wg(const Src &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus) {
     using W = Wg<NW, UPW, MODE, T, ST>;
-    const uint32_t lds_bytes = wg_layout(ST ? W::CAP : (nmax + 3) / 4).total;
+    if (nmax > 4 * W::CAP) return hipErrorInvalidValue;
+    constexpr uint32_t lds_bytes = wg_layout(W::CAP, W::CAP).total;
     const void *fn = reinterpret_cast<const void *>(&conv_wg_kernel<NW, UPW, MODE, T, ST, Src>);
-    // (LDS bytes << 32 | resident workgroups per CU) of the last launch shape
-    static std::atomic<uint64_t> occ{0}, lds_set{0};
+    static std::atomic<uint64_t> lds_set{0};
+    static std::atomic<int> occ{0};  // resident workgroups per CU
     hipError_t e = lds_limit_once(fn, lds_set);
     if (e != hipSuccess) return e;
-    uint64_t o = occ.load(std::memory_order_relaxed);
-    if ((o >> 32) != lds_bytes) {
-        int nblk = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nblk, fn, 64 * NW, lds_bytes);
+    int o = occ.load(std::memory_order_relaxed);
+    if (o == 0) {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, fn, 64 * NW, lds_bytes);
         if (e != hipSuccess) return e;
-        o = (uint64_t(lds_bytes) << 32) | uint32_t(nblk < 1 ? 1 : nblk);
+        if (o < 1) o = 1;
         occ.store(o, std::memory_order_relaxed);
     }
-    const uint64_t cap = uint64_t(uint32_t(o)) * uint64_t(num_cus > 0 ? num_cus : 1) * 8;
+    const uint64_t cap = uint64_t(o) * uint64_t(num_cus > 0 ? num_cus : 1) * 8;
     const uint32_t grid = uint32_t(std::min(count, cap));
     if (grid == 0) return hipSuccess;
     hipLaunchKernelGGL((conv_wg_kernel<NW, UPW, MODE, T, ST, Src>), dim3(grid), dim3(64 * NW), lds_bytes, st, src);

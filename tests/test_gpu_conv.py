@@ -213,3 +213,18 @@ def test_ragged_karatsuba_looping(B, orc, sizes, base, count):
         run_looping(B, c, orc, sizes, count, KARATSUBA)
     finally:
         c.close()
+
+
+# the sizes of workgroups of 8 and 16 waves (one or two units each), 12 and 16
+# chunks apart among them: the digit areas of successive products then differ
+# in length by as much as the waves' exchanged words lie apart
+@pytest.mark.parametrize("sizes,count", [((2048, 2045, 2000, 1984, 1100, 1036), 9000), ((4096, 4093, 4048, 4032, 2100), 4500),
+                                         ((8192, 8189, 8144, 8128, 4200), 4200)],
+                         ids=lambda v: str(v[0]) if isinstance(v, tuple) else "")
+def test_ragged_looping_waves(B, ctx, orc, sizes, count):
+    run_looping(B, ctx, orc, sizes, count, MFMA)
+
+
+def test_ragged_karatsuba_looping_waves(B, ctx, orc):
+    """Nine base products of 1025 .. 2048 words per instance (the default base)."""
+    run_looping(B, ctx, orc, (8192, 8189, 7936, 6000, 4097), 1100, KARATSUBA)
