@@ -224,8 +224,11 @@ __global__ __launch_bounds__(256) void bigadd_ragged_kernel(const uint32_t *__re
         const bi_desc d = desc[i];
         const uint32_t *ai = a + d.a_off * W, *bi_ = b + d.b_off * W;
         uint32_t *oi = out + d.out_off * W;
-        const uint32_t c = d.n_limbs > 64 ? add_instance_tail<U>(ai, bi_, oi, d.n_limbs * W, lane)
-                                          : add_instance_streamed<W, 1, false>(ai, bi_, oi, d.n_limbs, lane);
+        // 2^31 and more 64-bit limbs: 32 bits no longer count their words
+        const bool counted = W == 1 || d.n_limbs <= 0xFFFFFFFFu / W;
+        const uint32_t c = d.n_limbs <= 64 ? add_instance_streamed<W, 1, false>(ai, bi_, oi, d.n_limbs, lane)
+                           : counted       ? add_instance_tail<U>(ai, bi_, oi, d.n_limbs * W, lane)
+                                           : add_instance_streamed<W, U, false>(ai, bi_, oi, d.n_limbs, lane);
         if (carry && lane == 0) carry[i] = uint8_t(c);
     }
 }

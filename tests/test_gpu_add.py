@@ -233,3 +233,17 @@ def test_ragged_chunks(B, ctx, orc, limb_bits):
         s = slice(int(off[i]), int(off[i] + sizes[i]))
         e, c = orc.add(a[None, s], b[None, s])
         assert (got[s] == e[0]).all() and gc[i] == c[0], (i, sizes[i])
+
+
+@pytest.mark.timeout(110)
+def test_ragged_longest(B, ctx):
+    """2^31 limbs of 64 bits, more words than 32 bits count (16 GiB operands):
+    all ones plus itself."""
+    import torch
+    n = 1 << 31
+    a = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+    out = torch.zeros(n, dtype=torch.int64, device="cuda")
+    carry = G.zeros_u8(1)
+    B.bigadd_v(ctx, a, a, out, carry, G.desc_dev([0], [0], [0], [n]), 1, 64)
+    G.sync()
+    assert out[0].item() == -2 and bool((out[1:] == -1).all()) and carry.item() == 1
