@@ -434,14 +434,17 @@ static hipError_t launch_wu(const uint32_t *a, const uint32_t *b, uint32_t *o, u
         uint64_t waves = (batch + U - 1) / U;
         if (waves > max_waves) waves = max_waves;
         const dim3 g{uint32_t((waves + 3) / 4), 1, 1};
-        if (rows <= 2)
+        if (TAIL || rows <= 2) {  // ragged chunks: the caller's rule
             hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 2 ? U / 2 : 1), 2, NT, TAIL>), g, dim3(256), 0, st, a, b, o,
                                carry, len, batch);
-        else if (rows <= 4)
-            hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 4 ? U / 4 : 1), 4, NT, TAIL>), g, dim3(256), 0, st, a, b, o,
-                               carry, len, batch);
-        else
-            hipLaunchKernelGGL((bigadd_multi_kernel<W, 1, 8, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, len, batch);
+        } else if constexpr (!TAIL) {
+            if (rows <= 4)
+                hipLaunchKernelGGL((bigadd_multi_kernel<W, (U > 4 ? U / 4 : 1), 4, NT, TAIL>), g, dim3(256), 0, st, a, b,
+                                   o, carry, len, batch);
+            else
+                hipLaunchKernelGGL((bigadd_multi_kernel<W, 1, 8, NT, TAIL>), g, dim3(256), 0, st, a, b, o, carry, len,
+                                   batch);
+        }
     } else {
         // One workgroup per instance: NW waves x UC rows cover the instance
         // in one tile when it has at most 32 rows.
@@ -469,7 +472,14 @@ template <int W, bool TAIL>
 static hipError_t launch_w(const uint32_t *a, const uint32_t *b, uint32_t *o, uint8_t *carry, uint64_t m, uint32_t n,
                            uint64_t batch, hipStream_t st, const AddTune &t) {
     const uint64_t mw = t.max_waves;
-    const bool mu = (m <= 8 * 64) && ((m <= 2 * 64) ? t.multi2 : (m <= 4 * 64) ? t.multi4 : t.multi8);
+    // Ragged chunks: a wavefront per instance only for two rows and from 2^26
+    // words on (2^27 words of 270 / 450 words 310 / 321 us, a workgroup each
+    // 374 / 338).  Moving the words into place leaves one wavefront too long a
+    // chain: 600 instances of 257 / 385 / 769 words 5.2 / 5.4 / 8.7 us, as
+    // workgroups 3.8 / 3.7 / 3.8; 20000 13.3 / 17.2 / 33.8 and 14.3 / 17.2 /
+    // 30.8; 2^27 words of 577 / 1001 words 309 / 313 and 307 / 273.
+    const bool mu = TAIL ? t.multi2 && m <= 2 * 64 && n * batch >= uint64_t(1) << 26
+                         : m <= 8 * 64 && (m <= 2 * 64 ? t.multi2 : m <= 4 * 64 ? t.multi4 : t.multi8);
     if (t.nt) {
         if (t.rows == 2) return launch_wu<W, 2, true, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
         if (t.rows == 8) return launch_wu<W, 8, true, TAIL>(a, b, o, carry, m, n, batch, st, mw, mu);
@@ -506,8 +516,8 @@ hipError_t launch_bigadd(const void *a, const void *b, void *out, uint8_t *carry
     auto O = static_cast<uint32_t *>(out);
     if (cb == 16) return launch_w<4, false>(A, B, O, carry, m, n, batch, st, t);
     // Word-aligned instances of more than one narrow row: ragged 16-byte chunks
-    // (2^27 words of 65 / 257 / 577 / 1001 / 8191 words 540 / 470 / 636 / 423 /
-    // 321 -> 335 / 320 / 309 / 314 / 273 us).  Not 129 .. 192 words, whose 33 ..
+    // (2^27 words of 65 / 257 / 577 / 1001 / 8191 words 540 / 470 / 634 / 428 /
+    // 321 -> 335 / 325 / 307 / 273 / 273 us).  Not 129 .. 192 words, whose 33 ..
     // 48 chunks leave a row's other lanes idle (129 words: 336 -> 369), nor
     // 8-byte chunks (130 / 1022 words: 355 / 267 -> 377 / 306).
     if (cb == 4 && m > 64 && !(n > 128 && n <= 192)) return launch_w<4, true>(A, B, O, carry, (uint64_t(n) + 3) / 4, n, batch, st, t);

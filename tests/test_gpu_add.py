@@ -247,3 +247,24 @@ def test_ragged_longest(B, ctx):
     B.bigadd_v(ctx, a, a, out, carry, G.desc_dev([0], [0], [0], [n]), 1, 64)
     G.sync()
     assert out[0].item() == -2 and bool((out[1:] == -1).all()) and carry.item() == 1
+
+
+@pytest.mark.parametrize("n", [257, 258, 511])
+def test_word_aligned_long_batch(B, ctx, orc, n):
+    """Word-aligned instances of two rows from 2^26 words on (a wavefront
+    each): all instances compared, of 64 operand pairs."""
+    import torch
+    batch = (1 << 26) // n + 3
+    rng = np.random.default_rng(n)
+    a, b = (rng.integers(0, 2**32, (64, n), dtype=np.uint64).astype(np.uint32) for _ in range(2))
+    a[::4], b[::4] = 0xFFFFFFFF, 0
+    b[::4, 0] = 1
+    exp, cexp = (G.to_dev(x) if x.dtype == np.uint32 else torch.from_numpy(x).cuda() for x in orc.add(a, b))
+    which = torch.from_numpy(rng.integers(0, 64, batch)).cuda()
+    bufs = [torch.empty(batch * n + 1, dtype=torch.int32, device="cuda")[1:].reshape(batch, n) for _ in range(3)]
+    bufs[0].copy_(G.to_dev(a)[which])
+    bufs[1].copy_(G.to_dev(b)[which])
+    carry = G.zeros_u8(batch)
+    B.bigadd(ctx, *bufs, carry)
+    G.sync()
+    assert bool((bufs[2] == exp[which]).all()) and bool((carry == cexp[which]).all())
