@@ -207,11 +207,12 @@ __device__ __forceinline__ uint32_t add_instance_streamed(const uint32_t *__rest
     return cin_row;
 }
 
-// Ragged batch: one wavefront per descriptor, chunks of 16 bytes at any word
-// address above 64 limbs (one limb per lane at every size: 5000 instances of
-// 2^8 .. 2^18 bits 41 -> 20 us, 100 of 2^10 .. 2^18 27 -> 12), of one limb, W
-// words, in the one row of shorter ones (100000 of 2^8 .. 2^12 bits: 21 us, 26
-// in 16-byte chunks).
+// Ragged batch: one wavefront per descriptor.  Chunks of 16 bytes at any word
+// address above 128 limbs (one limb per lane at every size: 5000 instances of
+// 2^8 .. 2^18 bits 41 -> 20 us, 100 of 2^10 .. 2^18 27 -> 12); of one limb, W
+// words, in the two rows of shorter ones, both loaded at once (20000 of 2^11 ..
+// 2^11.9 bits 5.6 us, 6.7 in 16-byte chunks, 6.0 in four rows of limbs; in
+// 64-bit limbs and twice the bits 8.0, 8.5 and 9.6).
 template <int W, int U>
 __global__ __launch_bounds__(256) void bigadd_ragged_kernel(const uint32_t *__restrict__ a,
                                                             const uint32_t *__restrict__ b,
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(256) void bigadd_ragged_kernel(const uint32_t *__re
         uint32_t *oi = out + d.out_off * W;
         // 2^31 and more 64-bit limbs: 32 bits no longer count their words
         const bool counted = W == 1 || d.n_limbs <= 0xFFFFFFFFu / W;
-        const uint32_t c = d.n_limbs <= 64 ? add_instance_streamed<W, 1, false>(ai, bi_, oi, d.n_limbs, lane)
+        const uint32_t c = d.n_limbs <= 128 ? add_instance_streamed<W, 2, false>(ai, bi_, oi, d.n_limbs, lane)
                            : counted       ? add_instance_tail<U>(ai, bi_, oi, d.n_limbs * W, lane)
                                            : add_instance_streamed<W, U, false>(ai, bi_, oi, d.n_limbs, lane);
         if (carry && lane == 0) carry[i] = uint8_t(c);
