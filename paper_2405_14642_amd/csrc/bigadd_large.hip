@@ -35,11 +35,13 @@
 // Up to 8192 tiles (2^25 words) one kernel takes the place of the scan and the
 // two fix-up kernels, whose launches cost more than they do: a wave per tile
 // finds the tile's carry-in as above and adds it.  One pair of 3 2^20 / 2^22 /
-// 2^23 / 2^25 words: 16.5 / 17.3 / 25.8 / 73.6 -> 9.4 / 11.7 / 21.6 / 69.9 us per
-// call (all ones plus one 24.9 / 26.2 / 46.3 / 119.9 -> 19.3 / 20.9 / 41.6 /
-// 119.3).  Beyond, the search through long runs of propagating tiles, which
-// every wave repeats, outweighs it (2^29 words, all ones plus one: 1917 ->
-// 2798 us) and the launches no longer matter (2^27 words 271 -> 266 us).
+// 2^23 / 2^25 words: 13.4 / 15.5 / 25.1 / 73.5 -> 9.4 / 11.7 / 20.9 / 69.0 us per
+// call (all ones plus one 23.7 / 25.2 / 45.4 / 119.5 -> 19.0 / 20.6 / 40.7 /
+// 113.9; at word alignment, where 2^23 words are the limit, 30.0 -> 25.5 and
+// 41.9 -> 39.1).  Far beyond, the search through long runs of propagating tiles,
+// which every wave repeats, outweighs it (2^28 / 2^29 words, all ones plus one:
+// 947 / 1919 -> 976 / 2250 us) and the launches no longer matter (2^27 words
+// 269 -> 265 us).
 //
 // The chunk width W (16, 8 or 4 bytes) follows the pointers' alignment; the
 // integer's length need not be a multiple of it: the missing words of the
@@ -333,14 +335,16 @@ __device__ __forceinline__ uint32_t carry_from_below(const uint8_t *summary, uin
     for (int64_t top = (int64_t(t) - 64 + 15) / 16; top > 0; top -= 64) {
         const int64_t w = top - 1 - int64_t(lane);  // 16 tiles per word, nearest word first
         uint32_t found = 0, g = 0;
-        if (w >= 0) {
+        if (w >= 0) {  // all of the word's tiles lie below t
             const uint4 v = reinterpret_cast<const uint4 *>(summary)[w];
             const uint32_t in[4] = {v.x, v.y, v.z, v.w};
+            uint32_t at = 0;  // summaries of the four tiles that hold the highest found
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {  // the highest tile below t that does not only propagate
-                const uint32_t x = (in[j >> 2] >> (8 * (j & 3))) & 3u;
-                if (uint64_t(16 * w + j) < t && (x & 2u) == 0) { found = 1; g = x & 1u; }
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t x = ~in[j] & 0x02020202u;  // tiles that do not only propagate
+                if (x) { found = x; at = in[j]; }
             }
+            if (found) g = (at >> (30 - __builtin_clz(found))) & 1u;  // bit 0 of the byte whose bit 1 is the highest
         }
         stop = ballot(found != 0);
         if (stop) return uint32_t(__builtin_amdgcn_readlane(int(g), __builtin_ctzll(stop)));
