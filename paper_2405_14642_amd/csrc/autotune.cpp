@@ -57,13 +57,40 @@ bi_status time_us(hipStream_t st, Timer &t, int reps, F &&launch, float *us) {
 constexpr uint64_t kRaggedMax = 4096;  // instances of a ragged timing batch
 const int kAlgos[5] = {BI_MUL_SCHOOL_VALU, BI_MUL_SCHOOL_MFMA, BI_MUL_NTT, BI_MUL_NTT_PF64, BI_MUL_KARATSUBA};
 
+// Class k's VALU schedule: every (Q, waves) whose LDS fits is set in t and
+// timed by time(&us), the fastest kept.
+template <class F>
+bi_status tune_valu_schedule(Tune &t, uint32_t k, F &&time) {
+    float best = 0;
+    uint8_t bq = t.valu_q[k], bw = t.valu_nw[k];
+    bi_status s = BI_OK;
+    for (int Q : {2, 4}) {
+        for (int NW : {1, 2, 4, 8, 16}) {
+            if (s != BI_OK || !valu_plan_fits(class_nmax(k), Q, NW, nullptr)) continue;
+            t.valu_q[k] = uint8_t(Q);
+            t.valu_nw[k] = uint8_t(NW);
+            float us = 0;
+            s = time(&us);
+            if (s == BI_OK && (best == 0 || us < best)) {
+                best = us;
+                bq = uint8_t(Q);
+                bw = uint8_t(NW);
+            }
+        }
+    }
+    t.valu_q[k] = bq;
+    t.valu_nw[k] = bw;
+    return s;
+}
+
 // The list algorithm of class k from a ragged batch: instances of sizes
 // spread log-uniformly over the class (a fixed 64-bit LCG), operands at a +
 // i nmax and b + i nmax, results at o + 2 i nmax, launched as the one class
 // of a host-binned batch; every algorithm that runs the class is timed and
-// the fastest kept in c.tune.list_algo[k].
+// the fastest kept in c.tune.list_algo[k].  The VALU schedule comes first for
+// the classes whose uniform products do not use it (`schedule`).
 bi_status tune_ragged_class(Ctx &c, uint32_t k, const uint32_t *a, const uint32_t *b, uint32_t *o, uint64_t limbs,
-                            void *rdesc, hipStream_t st, Timer &tm) {
+                            void *rdesc, hipStream_t st, Timer &tm, bool schedule) {
     const uint32_t nmax = class_nmax(k), nmin = k ? nmax / 2 + 1 : 1;
     const uint64_t count = std::min<uint64_t>(limbs / nmax, kRaggedMax);
     std::vector<bi_desc> d(count);
@@ -90,15 +117,22 @@ bi_status tune_ragged_class(Ctx &c, uint32_t k, const uint32_t *a, const uint32_
     void *scr = nullptr;
     bi_status s = ctx_scratch(c, batch_scratch_bytes(count, c.num_cus), st, &scr);
     if (s != BI_OK) return s;
+    auto time_list = [&](int al, float *us) {
+        return time_us(st, tm, 3, [&]() {
+            return launch_bigmul_v_binned(c, c.tune, a, b, o, dd, dl, dc, hc, 32, al, scr, st) == hipSuccess ? BI_OK
+                                                                                                          : BI_EHIP;
+        }, us);
+    };
+    if (schedule) {
+        s = tune_valu_schedule(c.tune, k, [&](float *us) { return time_list(BI_MUL_SCHOOL_VALU, us); });
+        if (s != BI_OK) return s;
+    }
     float best = 0;
     int best_algo = c.tune.list_algo[k];
     for (int al : kAlgos) {
         if (!algo_supports(al, nmax)) continue;
         float us = 0;
-        s = time_us(st, tm, 3, [&]() {
-            return launch_bigmul_v_binned(c, c.tune, a, b, o, dd, dl, dc, hc, 32, al, scr, st) == hipSuccess ? BI_OK
-                                                                                                          : BI_EHIP;
-        }, &us);
+        s = time_list(al, &us);
         if (s != BI_OK) return s;
         if (best == 0 || us < best) {
             best = us;
@@ -126,39 +160,23 @@ bi_status autotune(Ctx &c, hipStream_t st, int *algo_out, uint32_t n_out) {
         (void)hipFree(buf);
         return set_error(BI_ENOMEM, "autotune buffers");
     }
-    const int algos[5] = {BI_MUL_SCHOOL_VALU, BI_MUL_SCHOOL_MFMA, BI_MUL_NTT, BI_MUL_NTT_PF64, BI_MUL_KARATSUBA};
     for (uint32_t k = 0; k < kNumClasses && s == BI_OK; ++k) {
         const uint32_t n = class_nmax(k);
         uint64_t batch = limbs / n;
         if (batch > 65536) batch = 65536;
-        // VALU schedule: every (Q, waves) whose LDS fits, fastest kept
-        {
-            float best_v = 0;
-            uint8_t bq = 0, bw = 0;
-            for (int Q : {2, 4}) {
-                for (int NW : {1, 2, 4, 8, 16}) {
-                    if (!valu_plan_fits(n, Q, NW, nullptr)) continue;
-                    c.tune.valu_q[k] = uint8_t(Q);
-                    c.tune.valu_nw[k] = uint8_t(NW);
-                    float us = 0;
-                    s = time_us(st, tm, 3, [&]() { return dispatch_bigmul(c, a, b, o, n, batch, BI_MUL_SCHOOL_VALU, st); },
-                                &us);
-                    if (s != BI_OK) break;
-                    if (best_v == 0 || us < best_v) {
-                        best_v = us;
-                        bq = uint8_t(Q);
-                        bw = uint8_t(NW);
-                    }
-                }
-                if (s != BI_OK) break;
-            }
-            c.tune.valu_q[k] = bq;
-            c.tune.valu_nw[k] = bw;
+        // VALU schedule, on the launches that it rules: the lists alone where
+        // uniform products are packed
+        const bool packed = n <= kPackedMaxWords;
+        if (!packed) {
+            s = tune_valu_schedule(c.tune, k, [&](float *us) {
+                return time_us(st, tm, 3, [&]() { return dispatch_bigmul(c, a, b, o, n, batch, BI_MUL_SCHOOL_VALU, st); },
+                               us);
+            });
             if (s != BI_OK) break;
         }
         float best = 0;
         int best_algo = c.tune.mul_algo[k];
-        for (int al : algos) {
+        for (int al : kAlgos) {
             if (!algo_supports(al, n)) continue;
             // Karatsuba: each base size that gives a different level count;
             // the class keeps the fastest base (whichever algorithm wins)
@@ -190,7 +208,7 @@ bi_status autotune(Ctx &c, hipStream_t st, int *algo_out, uint32_t n_out) {
         }
         c.tune.mul_algo[k] = best_algo;
         if (s != BI_OK) break;
-        s = tune_ragged_class(c, k, a, b, o, limbs, rdesc, st, tm);
+        s = tune_ragged_class(c, k, a, b, o, limbs, rdesc, st, tm, packed);
     }
     if (rdesc) (void)hipFree(rdesc);
     // Addition: workgroup-cooperative vs one wave per instance, per row class.

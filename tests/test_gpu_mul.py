@@ -422,3 +422,39 @@ def test_valu_schedules(B, orc):
             B.tune_set_valu(c, [(2, 3)] + [(0, 0)] * (B.NUM_CLASSES - 1))
     finally:
         c.close()
+
+
+def test_autotune_list_schedule(B):
+    """The VALU schedule of the classes up to 32 words rules their ragged lists
+    (uniform products are packed): the tuned one takes at most 1.4 times the
+    fastest one's time there (16 waves of Q = 2 take several times as long)."""
+    import torch
+    count, rng = 60000, np.random.default_rng(1)
+    buf = torch.randint(-2**31, 2**31, (32 * count,), dtype=torch.int64, device="cuda").to(torch.int32)
+    out = torch.empty(64 * count, dtype=torch.int32, device="cuda")
+    at = np.arange(count) * 32
+    c = B.Context(0)
+    try:
+        B.autotune(c)
+        tuned = B.tune_get_valu(c)
+
+        def time_us(k, schedule):
+            s = list(tuned)
+            s[k] = schedule
+            B.tune_set_valu(c, s)
+            best = float("inf")
+            for _ in range(7):
+                e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                e[0].record()
+                B.bigmul_v(c, buf, buf, out, desc[k], count, 32, algo=B.MUL_SCHOOL_VALU)
+                e[1].record()
+                e[1].synchronize()
+                best = min(best, 1e3 * e[0].elapsed_time(e[1]))
+            return best
+
+        desc = [G.desc_dev(at, at, 2 * at, rng.integers(lo, hi + 1, count)) for lo, hi in ((1, 16), (17, 32))]
+        for k in range(2):
+            times = {s: time_us(k, s) for s in ((q, w) for q in (2, 4) for w in (1, 2, 4, 8, 16))}
+            assert time_us(k, tuned[k]) <= 1.4 * min(times.values()), (k, tuned[k], times)
+    finally:
+        c.close()
