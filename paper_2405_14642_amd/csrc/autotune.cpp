@@ -83,63 +83,98 @@ bi_status tune_valu_schedule(Tune &t, uint32_t k, F &&time) {
     return s;
 }
 
-// The list algorithm of class k from a ragged batch: instances of sizes
-// spread log-uniformly over the class (a fixed 64-bit LCG), operands at a +
-// i nmax and b + i nmax, results at o + 2 i nmax, launched as the one class
-// of a host-binned batch; every algorithm that runs the class is timed and
-// the fastest kept in c.tune.list_algo[k].  The VALU schedule comes first for
-// the classes whose uniform products do not use it (`schedule`).
-bi_status tune_ragged_class(Ctx &c, uint32_t k, const uint32_t *a, const uint32_t *b, uint32_t *o, uint64_t limbs,
-                            void *rdesc, hipStream_t st, Timer &tm, bool schedule) {
-    const uint32_t nmax = class_nmax(k), nmin = k ? nmax / 2 + 1 : 1;
-    const uint64_t count = std::min<uint64_t>(limbs / nmax, kRaggedMax);
-    std::vector<bi_desc> d(count);
-    std::vector<uint32_t> list(count);
-    uint64_t x = 0x2405146420ull + k;
-    for (uint64_t i = 0; i < count; ++i) {
-        x = x * 6364136223846793005ull + 1442695040888963407ull;
-        const double u = double(x >> 11) * (1.0 / 9007199254740992.0);  // [0, 1)
-        uint32_t n = uint32_t(double(nmin) * std::pow(double(nmax) / double(nmin), u));
-        n = std::min(std::max(n, nmin), nmax);
-        d[i] = bi_desc{i * nmax, i * nmax, 2 * i * nmax, n, 0};
-        list[i] = uint32_t(i);
+// A host-binned ragged batch on the device: instances of sizes spread
+// log-uniformly over their class (a fixed 64-bit LCG), operands at a + off and
+// b + off, results at o + 2 off, lists in class order.
+struct RaggedBatch {
+    bi_desc *desc = nullptr;
+    uint32_t *list = nullptr, *counts = nullptr;
+    uint32_t host_counts[kNumClasses] = {};
+    uint64_t count = 0;
+};
+
+// `each` instances of every class in [k0, k1]; mem holds kRaggedMax
+// descriptors and list entries and the counts.
+bi_status ragged_batch(uint32_t k0, uint32_t k1, uint64_t each, void *mem, hipStream_t st, RaggedBatch *out) {
+    RaggedBatch r;
+    r.desc = static_cast<bi_desc *>(mem);
+    r.list = reinterpret_cast<uint32_t *>(r.desc + kRaggedMax);
+    r.counts = r.list + kRaggedMax;
+    std::vector<bi_desc> d;
+    std::vector<uint32_t> list;
+    uint64_t off = 0;
+    for (uint32_t k = k0; k <= k1; ++k) {
+        const uint32_t nmax = class_nmax(k), nmin = k ? nmax / 2 + 1 : 1;
+        uint64_t x = 0x2405146420ull + k;
+        for (uint64_t i = 0; i < each; ++i) {
+            x = x * 6364136223846793005ull + 1442695040888963407ull;
+            const double u = double(x >> 11) * (1.0 / 9007199254740992.0);  // [0, 1)
+            uint32_t n = uint32_t(double(nmin) * std::pow(double(nmax) / double(nmin), u));
+            n = std::min(std::max(n, nmin), nmax);
+            list.push_back(uint32_t(d.size()));
+            d.push_back(bi_desc{off, off, 2 * off, n, 0});
+            off += nmax;
+        }
+        r.host_counts[k] = uint32_t(each);
     }
-    auto *dd = static_cast<bi_desc *>(rdesc);
-    auto *dl = reinterpret_cast<uint32_t *>(dd + kRaggedMax);
-    auto *dc = dl + kRaggedMax;
-    uint32_t hc[kNumClasses] = {};
-    hc[k] = uint32_t(count);
-    if (hipMemcpyAsync(dd, d.data(), count * sizeof(bi_desc), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(dl, list.data(), count * sizeof(uint32_t), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(dc, hc, sizeof hc, hipMemcpyHostToDevice, st) != hipSuccess ||
+    r.count = d.size();
+    if (hipMemcpyAsync(r.desc, d.data(), r.count * sizeof(bi_desc), hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipMemcpyAsync(r.list, list.data(), r.count * sizeof(uint32_t), hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipMemcpyAsync(r.counts, r.host_counts, sizeof r.host_counts, hipMemcpyHostToDevice, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return set_error(BI_EHIP, "autotune descriptor copy");
+    *out = r;
+    return BI_OK;
+}
+
+// The list algorithm of class k from a ragged batch of the class: every
+// algorithm that runs it is timed and the fastest kept in c.tune.list_algo[k].
+// The VALU schedule comes first for the classes whose uniform products do not
+// use it (`schedule`).  The int8-MFMA classes that share one launch are timed
+// in it, in a batch of all of them, so that a class is moved out only if that
+// pays for its own launch.
+bi_status tune_ragged_class(Ctx &c, uint32_t k, const uint32_t *a, const uint32_t *b, uint32_t *o, uint64_t limbs,
+                            void *rdesc, hipStream_t st, Timer &tm, bool schedule) {
+    const uint32_t nmax = class_nmax(k);
+    const bool merged = k < kMergedClasses;
     void *scr = nullptr;
-    bi_status s = ctx_scratch(c, batch_scratch_bytes(count, c.num_cus), st, &scr);
+    bi_status s = ctx_scratch(c, batch_scratch_bytes(kRaggedMax, c.num_cus), st, &scr);
     if (s != BI_OK) return s;
-    auto time_list = [&](int al, float *us) {
-        return time_us(st, tm, 3, [&]() {
-            return launch_bigmul_v_binned(c, c.tune, a, b, o, dd, dl, dc, hc, 32, al, scr, st) == hipSuccess ? BI_OK
-                                                                                                          : BI_EHIP;
+    RaggedBatch r;
+    Tune t = c.tune;
+    auto time_list = [&](int al, int reps, float *us) {
+        t.list_algo[k] = al;
+        return time_us(st, tm, reps, [&]() {
+            return launch_bigmul_v_binned(c, t, a, b, o, r.desc, r.list, r.counts, r.host_counts, 32, BI_MUL_AUTO, scr,
+                                          st) == hipSuccess ? BI_OK : BI_EHIP;
         }, us);
     };
-    if (schedule) {
-        s = tune_valu_schedule(c.tune, k, [&](float *us) { return time_list(BI_MUL_SCHOOL_VALU, us); });
+    if (!merged || schedule) {
+        s = ragged_batch(k, k, std::min<uint64_t>(limbs / nmax, kRaggedMax), rdesc, st, &r);
         if (s != BI_OK) return s;
     }
+    if (schedule) {
+        s = tune_valu_schedule(t, k, [&](float *us) { return time_list(BI_MUL_SCHOOL_VALU, 10, us); });
+        if (s != BI_OK) return s;
+        c.tune.valu_q[k] = t.valu_q[k];
+        c.tune.valu_nw[k] = t.valu_nw[k];
+    }
+    if (merged) {
+        s = ragged_batch(0, kMergedClasses - 1, kRaggedMax / kMergedClasses, rdesc, st, &r);
+        if (s != BI_OK) return s;
+        for (uint32_t i = 0; i < kMergedClasses; ++i) t.list_algo[i] = BI_MUL_SCHOOL_MFMA;
+    }
     float best = 0;
-    int best_algo = c.tune.list_algo[k];
     for (int al : kAlgos) {
         if (!algo_supports(al, nmax)) continue;
         float us = 0;
-        s = time_list(al, &us);
+        s = time_list(al, merged ? 20 : 3, &us);
         if (s != BI_OK) return s;
         if (best == 0 || us < best) {
             best = us;
-            best_algo = al;
+            c.tune.list_algo[k] = al;
         }
     }
-    c.tune.list_algo[k] = best_algo;
     return BI_OK;
 }
 

@@ -124,14 +124,14 @@ template <class Cls, class Count>
 static hipError_t launch_classes(const Ctx &c, const Tune &tune, const Cls &cls, const Count &count, int algo, void *scr,
                                  hipStream_t st) {
     SmallLists small{};
-    uint64_t small_count[4] = {};
+    uint64_t small_count[kMergedClasses] = {};
     for (uint32_t k = 0; k < kNumClasses; ++k) {
         const uint64_t n = count(k);
         if (n == 0) continue;
         const uint32_t nmax = class_nmax(k);
         int alg = tune.list_algo[k];
         if (algo != BI_MUL_AUTO && algo_supports(algo, nmax)) alg = algo;
-        if (k < 4 && alg == BI_MUL_SCHOOL_MFMA) {
+        if (k < kMergedClasses && alg == BI_MUL_SCHOOL_MFMA) {
             small.cls[k] = cls(k);
             small_count[k] = n;
             continue;

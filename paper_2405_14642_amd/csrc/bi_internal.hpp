@@ -278,14 +278,15 @@ hipError_t launch_bigmul_mfma_list(const ListInst &src, uint32_t nmax, uint64_t 
                                    int num_cus);
 constexpr uint32_t kConvSmallMax = 128;
 hipError_t launch_conv_small_full(const UniformInst &src, hipStream_t st, int num_cus);
-// The first four ragged classes (up to 128 words) in one launch of at most
+// The first ragged classes (up to 128 words) in one launch of at most
 // count[k] instances each (0: none; cls[k] is not read then); launch fills in
 // the block ranges.
+constexpr uint32_t kMergedClasses = 4;
 struct SmallLists {
-    ListInst cls[4];
-    uint32_t first[5];
+    ListInst cls[kMergedClasses];
+    uint32_t first[kMergedClasses + 1];
 };
-hipError_t launch_conv_small_lists(SmallLists p, const uint64_t (&count)[4], hipStream_t st, int num_cus);
+hipError_t launch_conv_small_lists(SmallLists p, const uint64_t (&count)[kMergedClasses], hipStream_t st, int num_cus);
 hipError_t launch_conv_small_list(const ListInst &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus);
 
 // Low product (mod 2^N) or (poly) the polynomial program of n-word instances

@@ -458,3 +458,38 @@ def test_autotune_list_schedule(B):
             assert time_us(k, tuned[k]) <= 1.4 * min(times.values()), (k, tuned[k], times)
     finally:
         c.close()
+
+
+def test_autotune_merged_classes(B):
+    """Short classes share one launch in a mixed batch; tuning moves a class
+    out of it only if that pays for its own launch, so a tuned context takes at
+    most 1.25 times the merged launch's time."""
+    import torch
+    count = 1000
+    n = np.random.default_rng(2).integers(1, 129, count)
+    at = np.arange(count) * 128
+    buf = torch.randint(-2**31, 2**31, (128 * count,), dtype=torch.int64, device="cuda").to(torch.int32)
+    out = torch.empty(256 * count, dtype=torch.int32, device="cuda")
+    desc = G.desc_dev(at, at, 2 * at, n)
+    c = B.Context(0)
+    try:
+        B.autotune(c)
+        tuned = B.tune_get_list(c)
+
+        def time_us(algos):
+            B.tune_set_list(c, algos)
+            best = float("inf")
+            for _ in range(15):
+                e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                e[0].record()
+                for _ in range(5):
+                    B.bigmul_v(c, buf, buf, out, desc, count, 32)
+                e[1].record()
+                e[1].synchronize()
+                best = min(best, 200 * e[0].elapsed_time(e[1]))
+            return best
+
+        merged = time_us([B.MUL_SCHOOL_MFMA] * 4 + tuned[4:])
+        assert time_us(tuned) <= 1.25 * merged, (tuned, merged)
+    finally:
+        c.close()
