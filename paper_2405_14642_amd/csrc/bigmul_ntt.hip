@@ -1300,25 +1300,20 @@ struct LargeCoef {
 // lines take 6.5 / 13.5.
 constexpr uint32_t kLargeTileWords = 8 * 256;
 
-// Tile status from the threads' 8-word sums (carry out g, all-ones p), and
-// the carry into each thread given the carry cin into the tile.  summary:
-// 4 LDS words.  Returns the carry into the calling thread.
-__device__ __forceinline__ uint32_t tile_carries(uint32_t g, bool p, uint32_t cin, uint32_t *summary,
-                                                 uint8_t *status) {
+// The carry into the calling thread given the carry cin into its tile, from
+// the threads' 8-word sums (carry out g, all-ones p).  summary: 4 LDS words.
+__device__ __forceinline__ uint32_t tile_carries(uint32_t g, bool p, uint32_t cin, uint32_t *summary) {
     const uint32_t lane = lane_id(), w = wave_in_block();
     const uint64_t G = ballot(g != 0), P = ballot(p);
     const WaveCarry w0 = wave_carry(G, P, 0);
     if (lane == 0) summary[w] = w0.out | ((P == ~0ull ? 1u : 0u) << 1);
     __syncthreads();
-    uint32_t c = cin, tg = 0, tp = 1;
+    uint32_t c = cin;
 #pragma unroll
     for (uint32_t v = 0; v < 4; ++v) {
         const uint32_t sv = summary[v];
         if (v < w) c = (sv & 1u) | ((sv >> 1) & c);
-        tg = (sv & 1u) | ((sv >> 1) & tg);
-        tp &= sv >> 1;
     }
-    if (status) *status = uint8_t(tg | (tp << 1));
     __syncthreads();  // summary is free again
     return uint32_t(wave_carry(G, P, c).into >> lane) & 1u;
 }
@@ -1450,7 +1445,7 @@ __global__ __launch_bounds__(256) void large_ntt_add_kernel(const uint32_t *__re
         bool ones = false;
         const uint32_t gc = fold_sum8(lw, hw, sm, ones);
         __syncthreads();
-        const uint32_t c = tile_carries(gc, ones, tile_cin, summary, nullptr);
+        const uint32_t c = tile_carries(gc, ones, tile_cin, summary);
         add_carry_words<8>(sm, c);
         const uint32_t s0[4] = {sm[0], sm[1], sm[2], sm[3]}, s1[4] = {sm[4], sm[5], sm[6], sm[7]};
         sink(2 * g, s0);

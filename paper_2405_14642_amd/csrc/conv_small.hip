@@ -74,47 +74,47 @@ __device__ __forceinline__ void small_full(const Src &src, uint8_t *lds, uint64_
     const LaneAddr la = lane_addr();
     const uint8_t *ap = lds + la.a, *bp = lds + S::AB + 16 * S::kPad + la.b;
     const uint32_t co = lane & (16 * TPI - 1), oslot = lane / (16 * TPI);  // output chunk of this lane
-            // operand chunk of this lane
-            const uint32_t half = lane >> 5, l = lane & 31u;
-            const uint32_t slot = l / S::CPI, c = l & (S::CPI - 1);
-            const uint64_t keep = TPI == 4 ? ~0x8000000080000000ull : TPI == 2 ? ~0x8000800080008000ull : ~0x8080808080808080ull;
-            uint8_t *dst = lds + slot * S::INST + (half ? S::AB + 16 * (S::kPad + c) : kAPad + 16 * c);
-            uint32_t *tdst = reinterpret_cast<uint32_t *>(dst + 16 + (half ? 12 : 0));  // digit D of the operand
-            auto fetch = [&](uint64_t g, uint32_t (&x)[4], uint32_t &n) {
-                const uint64_t inst = g * S::IPW + slot;
-                n = 0;
-                if (inst < count) {
-                    const InstRef in = src.get(inst);
-                    n = in.n;
-                    load_chunk4(half ? in.b : in.a, in.n, c, x);
-                }
-            };
-            uint32_t xn[4] = {0, 0, 0, 0}, nn = 0;
-            uint64_t g = first;
-            if (g < groups) fetch(g, xn, nn);
-            for (; g < groups; g += stride) {
-                uint32_t x[4] = {xn[0], xn[1], xn[2], xn[3]};
-                const uint32_t n = nn;
-                if (g + stride < groups) fetch(g + stride, xn, nn);
-                const bool digits = 4 * c < n;
-                if (!digits) { x[0] = x[1] = x[2] = x[3] = 0; }
-                const uint32_t t = recode_lane(x, digits, keep, lane);
-                wave_lds_fence();
-                const uint4 rv = reversed(x);
-                *reinterpret_cast<uint4 *>(dst) = half ? rv : make_uint4(x[0], x[1], x[2], x[3]);
-                if (c == S::CPI - 1) *tdst = half ? t << 24 : t;
-                wave_lds_fence();
-                v4i acc[4] = {};
-    #pragma unroll
-                for (int i = 0; i < S::IPW; ++i) small_steps<TPI, false>(ap + i * S::INST, la.sh, bp + i * S::INST, acc + i * TPI);
-                uint32_t s[4];
-                small_finish<TPI, false>(acc, s, lane, s);
-                const uint64_t oi = g * S::IPW + oslot;
-                if (oi < count) {
-                    const InstRef out = src.get(oi);
-                    store_chunk4(out.c, 2 * out.n, co, s, src.streams());
-                }
-            }
+    // operand chunk of this lane
+    const uint32_t half = lane >> 5, l = lane & 31u;
+    const uint32_t slot = l / S::CPI, c = l & (S::CPI - 1);
+    const uint64_t keep = TPI == 4 ? ~0x8000000080000000ull : TPI == 2 ? ~0x8000800080008000ull : ~0x8080808080808080ull;
+    uint8_t *dst = lds + slot * S::INST + (half ? S::AB + 16 * (S::kPad + c) : kAPad + 16 * c);
+    uint32_t *tdst = reinterpret_cast<uint32_t *>(dst + 16 + (half ? 12 : 0));  // digit D of the operand
+    auto fetch = [&](uint64_t g, uint32_t (&x)[4], uint32_t &n) {
+        const uint64_t inst = g * S::IPW + slot;
+        n = 0;
+        if (inst < count) {
+            const InstRef in = src.get(inst);
+            n = in.n;
+            load_chunk4(half ? in.b : in.a, in.n, c, x);
+        }
+    };
+    uint32_t xn[4] = {0, 0, 0, 0}, nn = 0;
+    uint64_t g = first;
+    if (g < groups) fetch(g, xn, nn);
+    for (; g < groups; g += stride) {
+        uint32_t x[4] = {xn[0], xn[1], xn[2], xn[3]};
+        const uint32_t n = nn;
+        if (g + stride < groups) fetch(g + stride, xn, nn);
+        const bool digits = 4 * c < n;
+        if (!digits) { x[0] = x[1] = x[2] = x[3] = 0; }
+        const uint32_t t = recode_lane(x, digits, keep, lane);
+        wave_lds_fence();
+        const uint4 rv = reversed(x);
+        *reinterpret_cast<uint4 *>(dst) = half ? rv : make_uint4(x[0], x[1], x[2], x[3]);
+        if (c == S::CPI - 1) *tdst = half ? t << 24 : t;
+        wave_lds_fence();
+        v4i acc[4] = {};
+#pragma unroll
+        for (int i = 0; i < S::IPW; ++i) small_steps<TPI, false>(ap + i * S::INST, la.sh, bp + i * S::INST, acc + i * TPI);
+        uint32_t s[4];
+        small_finish<TPI, false>(acc, s, lane, s);
+        const uint64_t oi = g * S::IPW + oslot;
+        if (oi < count) {
+            const InstRef out = src.get(oi);
+            store_chunk4(out.c, 2 * out.n, co, s, src.streams());
+        }
+    }
 }
 
 }  // namespace

@@ -120,7 +120,7 @@ __device__ __forceinline__ void unit_steps(const uint8_t *ap, uint32_t sh, const
                 }
             }
         }
-if (m < end) {  // fewer than eight steps left
+        if (m < end) {  // fewer than T steps left
             const int32_t least = k == 0 ? -2 : -1, cnt = end - m;
             const uint8_t *am = ak + 256 * m;
             v4i w[T];
@@ -264,7 +264,7 @@ struct Wg {
     }
 
     // The product of the digits in LDS plus the words `add`: on return
-    // s[2 u + i] holds chunk `lane` of row 2 unit(u) + i.  Two barriers; the
+    // s[RU u + i] holds chunk `lane` of row RU unit(u) + i.  Two barriers; the
     // digit areas are free after the first.
     template <bool ADD>
     __device__ __forceinline__ void product(const uint32_t (&add)[RW][4], uint32_t (&s)[NR][4]) const {
@@ -514,10 +514,9 @@ hipError_t launch_conv_fused(bool poly, const uint32_t *a, const uint32_t *b, ui
     if (n <= 512) return BI_WG(1, true);
     if (poly && n <= 768) return launch_wg<1, 1, kPoly, 12, true>(src, n, batch, st, num_cus);
     if (poly && n <= 1024) return launch_wg<1, 1, kPoly, 16, true>(src, n, batch, st, num_cus);
-    if (poly && n > 1024 && n <= 1536) return launch_wg<3, 1, kPoly, 8, false>(src, n, batch, st, num_cus);
     if (!poly && n <= 768) return launch_wg<1, 1, kLow, 12, true>(src, n, batch, st, num_cus);
     if (!poly && n <= 1024) return launch_wg<1, 1, kLow, 16, true>(src, n, batch, st, num_cus);
-    if (n <= 1024) return BI_WG(2, false);
+    if (poly && n <= 1536) return launch_wg<3, 1, kPoly, 8, false>(src, n, batch, st, num_cus);
     if (n <= 2048) return BI_WG(4, false);
     if (n <= 4096) return BI_WG(8, false);
     return BI_WG(16, false);
