@@ -228,3 +228,15 @@ def test_ragged_looping_waves(B, ctx, orc, sizes, count):
 def test_ragged_karatsuba_looping_waves(B, ctx, orc):
     """Nine base products of 1025 .. 2048 words per instance (the default base)."""
     run_looping(B, ctx, orc, (8192, 8189, 7936, 6000, 4097), 1100, KARATSUBA)
+
+
+# Poly of 33 to 36 words: several to a wavefront on the VALU up to 1000 instances
+@pytest.mark.parametrize("batch", [1, 999, 1000, 1001])
+@pytest.mark.parametrize("n", [33, 35, 36, 37])
+def test_poly_few(B, ctx, n, batch):
+    import oracle as O
+    a, b = operands(n + batch, batch, n)
+    out = G.empty_dev((batch, n), np.uint32)
+    B.fused(ctx, PROG_POLY, G.to_dev(a), G.to_dev(b), out)
+    G.sync()
+    assert differing(G.from_dev(out, np.uint32), O.poly(a, b)) == []
