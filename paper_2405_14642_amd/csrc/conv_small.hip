@@ -8,8 +8,8 @@
 // the time a product takes, and a third of it in HBM traffic: seven waves per
 // SIMD that never wait for each other overlap them.  Measured, full products
 // (one workgroup per product before, int8 windows in LDS at 128 words and the
-// VALU schoolbook at 32): 65536 x 128 words 83.3 -> 40.7 us (3.3 TB/s),
-// 262144 x 32 words 213 -> 38.0 us (3.5 TB/s).
+// VALU schoolbook at 32): 65536 x 128 words 83.3 -> 37.1 us (3.6 TB/s),
+// 262144 x 32 words 213 -> 33.7 us (4.0 TB/s).
 // Full products hold a's chunks in lanes 0..31 and b's in lanes 32..63, so
 // both operands are recoded by one carry scan.
 #include <algorithm>
@@ -230,7 +230,10 @@ __global__ __launch_bounds__(256, 5) void conv_small_lists_kernel(SmallLists p) 
 }
 
 hipError_t launch_conv_small_lists(SmallLists p, const uint64_t (&count)[4], hipStream_t st, int num_cus) {
-    const uint64_t cap = uint64_t(num_cus > 0 ? num_cus : 1) * 4;  // blocks per class: they loop beyond it
+    // blocks per class, which loop beyond that: one per CU would take 67 us for
+    // 20000 products of 1 .. 128 words and 801 for 400000, four take 58 and 578,
+    // sixteen 58.5 and 557
+    const uint64_t cap = uint64_t(num_cus > 0 ? num_cus : 1) * 4;
     const uint32_t ipw[4] = {4, 4, 2, 1};
     p.first[0] = 0;
     for (int k = 0; k < 4; ++k)

@@ -22,11 +22,21 @@
 // (T = 16 at two or three: 2048 words 99 -> 97-103 us, 1500 words 119 ->
 // 127-152).  Measured against the kernels before it (32 x 32 x 32 tiles over
 // 8-byte windows of a in LDS; three kernels and global scratch above 1024
-// words), full products: 16384 x 256 words 51.9 -> 24.5 us, 8192 x 512 words
-// 61.7 -> 28, 4096 x 1024 words 81.4 -> 54, 2048 x 2048 words 198 -> 95, 512 x
-// 4096 words 196 -> 87 us.  Low products and Poly against the VALU schoolbook
-// in LDS: 16384 x 512 words 266 -> 40 us, 4096 x 2048 words (Poly) 3041 ->
-// 390, 128 x 8192 words 657 -> 70 and (Poly) 2631 -> 277.
+// words), full products: 16384 x 256 words 51.9 -> 23 us, 8192 x 512 words
+// 61.7 -> 30, 4096 x 1024 words 81.4 -> 57, 2048 x 2048 words 198 -> 97, 512 x
+// 4096 words 196 -> 90 us.  Up to 64 products of more than 5500 words are
+// the exception: each keeps one CU busy for longer than the three kernels,
+// which spread it over several, took in all (1 / 32 products of
+// 8192 words 91 / 96 -> 128 / 130 us, of 6000 words 69 / 73 -> 74 / 75); the
+// default there is Karatsuba (32 and 29 us for one).  Low products and Poly
+// against the VALU schoolbook in LDS: 16384 x 512 words 266 -> 35.5 us, 4096 x
+// 2048 words (Poly) 3041 -> 375, 128 x 8192 words 657 -> 70 and (Poly) 2631 ->
+// 279.
+//
+// Registers: the bounds of the kernel make the compiler spill in Poly (16 words
+// per lane for up to 2048 words, 31 and 33 above, 24 for 769 .. 1024) and in
+// full products of two units per wave (17 above 4096 words) and of 641 .. 768
+// words (5), and 4 in low products above 2048 words.
 #include <algorithm>
 #include <atomic>
 #include <utility>
@@ -464,11 +474,12 @@ static hipError_t launch_wg(const Src &src, uint32_t nmax, uint64_t count, hipSt
 }
 
 // Full products by size: one straight-line wave while its T = 4 tiles per 128
-// words fit the registers (up to 640 words: 2^24 words of 300 / 512 / 600
-// words take 121 / 110 / 122 us, in loops over two or three units 186 / 142 /
-// 190), two of them up to 768 words and above 896 (111 / 104 us, loops 140 /
-// 111; between the two the padding to 1024 costs more than it saves: 800
-// words 160, loops 143), else loops over one unit of 256 words per wave.
+// words fit the registers (up to 640 words: batches of 2^24 words, but at most
+// 2^33 products of words, of 300 / 512 / 600 words take 121 / 110 / 122 us, in
+// loops over two or three units 186 / 142 / 190), two of them up to 768 words
+// and above 896 (768 / 1024 words 111 / 104 us, loops 140 / 111; between the two
+// the padding to 1024 costs more than it saves: 800 words 160, loops 143), else
+// loops over one unit of 256 words per wave.
 template <class Src>
 static hipError_t launch_full(const Src &src, uint32_t nmax, uint64_t count, hipStream_t st, int num_cus) {
     if (nmax <= 256) return launch_wg<1, 1, kFull, 8, true>(src, nmax, count, st, num_cus);
@@ -505,9 +516,9 @@ hipError_t launch_conv_fused(bool poly, const uint32_t *a, const uint32_t *b, ui
     if (n > kMaxLimbs32) return hipErrorInvalidValue;
     const LowInst src{{a, b, c, n, batch, streamed_results(4 * uint64_t(n) * batch)}};
     if (n <= kConvSmallLowMax) return launch_conv_small_low(poly, src, st, num_cus);
-    // Up to 1024 words one straight-line wave (2^24 words of 600 / 768 / 1024
-    // words: 90 / 58 / 54 us, Poly 335 / 236 / 197; in loops over units of 512
-    // words 142 / 101 / 62 and 546 / 393 / 236), above it a wave per unit.
+    // Up to 1024 words one straight-line wave (the same batches of 600 / 768 /
+    // 1024 words: 90 / 58 / 54 us, Poly 335 / 236 / 197; in loops over units of
+    // 512 words 142 / 101 / 62 and 546 / 393 / 236), above it a wave per unit.
 #define BI_WG(W, ST)                                                 \
     poly ? launch_wg<W, 1, kPoly, 8, ST>(src, n, batch, st, num_cus) \
          : launch_wg<W, 1, kLow, 8, ST>(src, n, batch, st, num_cus)

@@ -57,8 +57,8 @@ size_t uniform_algo_scratch_bytes(int alg, uint32_t n32) {
 // the VALU schoolbook up to 16 limbs (2^22 words of 4 / 16 limbs take 16 / 21
 // us, the int8-MFMA schoolbook 97 / 29), that one up to 4096 limbs (2^17 bits;
 // 2^22 words of 20 / 32 / 64 limbs take 25 / 17 / 20 us, the VALU schoolbook
-// 33 / 32 / 74), Karatsuba at 8192 limbs (64 products: 63 us, the MFMA
-// schoolbook 138, the two-prime NTT 78; 6000 limbs: 53 / 80 / 74).  Ragged
+// 33 / 30 / 74), Karatsuba at 8192 limbs (64 products: 64 us, the MFMA
+// schoolbook 131, the two-prime NTT 80; 6000 limbs: 53 / 75 / 76).  Ragged
 // batches (sizes spread over each class; on the VALU a workgroup each): the
 // int8-MFMA schoolbook up to 4096 limbs, Karatsuba over 8192.  Karatsuba's base is 2048 limbs in the
 // two largest classes (8192 x 64: 62.7 us, 66.2 over 1024; 4096 x 256: 56.8,

@@ -90,8 +90,8 @@ def test_workgroup_many(B, ctx, orc):
 @pytest.mark.parametrize("sizes", [np.arange(1, 129), np.r_[129:257:3, 257:513:7, 513:1025:19],
                                    np.r_[1025:2049:101, 2049:4097:307, 4097:8193:1023]], ids=["small", "mid", "large"])
 def test_ragged(B, ctx, orc, sizes):
-    """Sizes of every class twice over and shuffled, so that a wave or a
-    workgroup meets longer and shorter instances in turn."""
+    """Sizes of every class twice over and shuffled, each instance on a wave or
+    workgroup of its own."""
     n = np.random.default_rng(3).permutation(np.repeat(sizes, 2))
     off = np.concatenate([[0], np.cumsum(n)[:-1]])
     rng = np.random.default_rng(4)
